@@ -92,7 +92,7 @@ dt_status dt_bvh_bytes(int32_t nv, int32_t nf, size_t* bvh_bytes, size_t* ws_byt
  * linear BVH (63-bit Morton codes of face centroids, their top 32 bits up to
  * 2^20 faces, stable radix sort, binary
  * radix tree with index tie-break, bottom-up box fit, then small treelets
- * restructured for least box surface area, and a quantized 4-wide tree
+ * restructured for least box surface area, and a quantized 6-wide tree
  * collapsed from it for traversal).  Call again whenever V
  * changes.  Face indices must lie in [0, nv) (checked on the device only
  * through DT_FLAG results, not here: the caller guarantees it). */

@@ -36,38 +36,40 @@ __global__ void k_fill_u32(uint32_t* p, uint32_t v, int64_t n) {
     p[i] = v;
 }
 
-__global__ void k_scan_reduce(const int32_t* in, int32_t n, int32_t chunk, int32_t* part) {
-  __shared__ int32_t sh[SCAN_T];
+template <class T>
+__global__ void k_scan_reduce(const T* in, int32_t n, int32_t chunk, T* part) {
+  __shared__ T sh[SCAN_T];
   int64_t lo = (int64_t)blockIdx.x * chunk;
   int64_t hi = lo + chunk < n ? lo + chunk : n;
-  int32_t s = 0;
+  T s = 0;
   for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) s += in[i];
-  int32_t tot = block_incl_scan(s, sh);
+  T tot = block_incl_scan(s, sh);
   if (threadIdx.x == blockDim.x - 1) part[blockIdx.x] = tot;
 }
 
 // exclusive scan of part[0..nb) in place; part[nb] = total
-__global__ void k_scan_partials(int32_t* part, int nb) {
-  __shared__ int32_t sh[SCAN_NB];
+template <class T>
+__global__ void k_scan_partials(T* part, int nb) {
+  __shared__ T sh[SCAN_NB];
   int t = threadIdx.x;
-  int32_t v = t < nb ? part[t] : 0;
-  int32_t inc = block_incl_scan(v, sh);
+  T v = t < nb ? part[t] : 0;
+  T inc = block_incl_scan(v, sh);
   __syncthreads();
   if (t < nb) part[t] = inc - v;
   if (t == (int)blockDim.x - 1) part[nb] = inc;
 }
 
-__global__ void k_scan_apply(const int32_t* in, int32_t* out, int32_t n, int32_t chunk,
-                             const int32_t* part) {
-  __shared__ int32_t sh[SCAN_T];
+template <class T>
+__global__ void k_scan_apply(const T* in, T* out, int32_t n, int32_t chunk, const T* part) {
+  __shared__ T sh[SCAN_T];
   int64_t lo = (int64_t)blockIdx.x * chunk;
   int64_t hi = lo + chunk < n ? lo + chunk : n;
-  int32_t carry = part[blockIdx.x];
+  T carry = part[blockIdx.x];
   for (int64_t base = lo; base < hi; base += blockDim.x) {
     int64_t i = base + threadIdx.x;
-    int32_t v = i < hi ? in[i] : 0;
-    int32_t inc = block_incl_scan(v, sh);
-    int32_t tot = sh[blockDim.x - 1];
+    T v = i < hi ? in[i] : 0;
+    T inc = block_incl_scan(v, sh);
+    T tot = sh[blockDim.x - 1];
     if (i < hi) out[i] = carry + inc - v;
     carry += tot;
     __syncthreads();
@@ -381,12 +383,19 @@ __device__ __forceinline__ int fenc(float f) {
 }
 __device__ __forceinline__ float fdec(int i) { return __int_as_float(i >= 0 ? i : i ^ 0x7FFFFFFF); }
 
-__global__ void k_fit_init(int* acc, int n_nodes) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < 6 * n_nodes; i += gridDim.x * blockDim.x)
+// box accumulators empty, arrival counters and k_cut's membership masks zero
+__global__ void k_fit_init(int* acc, int32_t* arrive, int32_t* member, int n_nodes) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < 6 * (int64_t)n_nodes;
+       i += (int64_t)gridDim.x * blockDim.x) {
     acc[i] = (i % 6) < 3 ? fenc(INFINITY) : fenc(-INFINITY);
+    if (i < n_nodes) {
+      arrive[i] = 0;
+      member[i] = 0;
+    }
+  }
 }
 
-// Leaves in Morton order get their triangle; boxes are fitted bottom-up.
+// Boxes are fitted bottom-up from the triangles in Morton order.
 // Each child writes its box into its slot of the parent node (read only by
 // later kernels) and merges it into the parent's union accumulator with
 // device-scope atomic min / max.  The second child to arrive (arrival
@@ -402,10 +411,12 @@ __global__ void k_fit(const float* V, const int32_t* F, int32_t nv, const int32_
   int f = sorted[j];
   v3 a = load3(V + 3 * vclamp(F[3 * f], nv)), b = load3(V + 3 * vclamp(F[3 * f + 1], nv));
   v3 c = load3(V + 3 * vclamp(F[3 * f + 2], nv));
-  leaves[3 * j + 0] = make_float4(a.x, a.y, a.z, __int_as_float(f));
-  leaves[3 * j + 1] = make_float4(b.x, b.y, b.z, 0.f);
-  leaves[3 * j + 2] = make_float4(c.x, c.y, c.z, 0.f);
-  if (n == 1) return;
+  if (n == 1) {  // no tree: the one leaf (k_wide_write writes them otherwise)
+    leaves[0] = make_float4(a.x, a.y, a.z, __int_as_float(f));
+    leaves[1] = make_float4(b.x, b.y, b.z, 0.f);
+    leaves[2] = make_float4(c.x, c.y, c.z, 0.f);
+    return;
+  }
   v3 lo = vmin(vmin(a, b), c), hi = vmax(vmax(a, b), c);
   int ref = (int)((uint32_t)j | DT_LEAF_BIT);
   int p = leaf_parent[j];
@@ -437,10 +448,8 @@ __global__ void k_fit(const float* V, const int32_t* F, int32_t nv, const int32_
   }
 }
 
-// 1 for an internal node at even depth (root = 0), else 0: walk to the root.
-// With hdr, also the tree height (root = 1): the deepest internal node has a
-// leaf child one level below it.
-__global__ void k_even(int32_t n_int, const BvhNode* nodes, int32_t* flag, BvhHeader* hdr) {
+// 1 for an internal node at even depth (root = 0), else 0: walk to the root
+__global__ void k_even(int32_t n_int, const BvhNode* nodes, int32_t* flag) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_int) return;
   int dep = 0, p = i;
@@ -449,7 +458,6 @@ __global__ void k_even(int32_t n_int, const BvhNode* nodes, int32_t* flag, BvhHe
     ++dep;
   }
   flag[i] = (dep & 1) == 0;
-  if (hdr) atomicMax(&hdr->depth, dep + 2);
 }
 
 // ------------------------------------------------------------------ treelet restructuring
@@ -614,89 +622,266 @@ __device__ __forceinline__ int quant_exponent(float lo, float hi) {
   return e;
 }
 
-// Writes the 4-wide node of every even-depth internal node i at index idx[i]:
-// each leaf child keeps its slot, each internal child hands over its two
-// children (their boxes are stored in that child's node).
-__global__ void k_collapse(int32_t n_int, const BvhNode* nodes, const int32_t* flag,
-                           const int32_t* idx, Bvh4Node* out, int32_t cap4) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_int || !flag[i]) return;
-  int j = idx[i];
-  if (j < 0 || j >= cap4) return;
-  float lo[4][3], hi[4][3];
-  uint32_t ch[4];
-  int k = 0;
-  auto ref = [&](uint32_t c) -> uint32_t {
-    if (c & DT_LEAF_BIT) return c;
-    return c < (uint32_t)n_int ? (uint32_t)idx[c] : DT_NO_CHILD;
-  };
-  auto put = [&](const BvhNode& m, int side, uint32_t c) {
-    const float4 a = m.a, b = m.b, cc = m.c;
-    if (side == 0) {
-      lo[k][0] = a.x, lo[k][1] = a.y, lo[k][2] = a.z;
-      hi[k][0] = a.w, hi[k][1] = b.x, hi[k][2] = b.y;
-    } else {
-      lo[k][0] = b.z, lo[k][1] = b.w, lo[k][2] = cc.x;
-      hi[k][0] = cc.y, hi[k][1] = cc.z, hi[k][2] = cc.w;
-    }
-    ch[k] = ref(c);
-    ++k;
-  };
-  const BvhNode n = nodes[i];
-  uint32_t cs[2] = {(uint32_t)n.d.x, (uint32_t)n.d.y};
-  for (int side = 0; side < 2; ++side) {
-    uint32_t c = cs[side];
-    if ((c & DT_LEAF_BIT) || c >= (uint32_t)n_int) {
-      put(n, side, c);
-    } else {
-      const BvhNode m = nodes[c];
-      put(m, 0, (uint32_t)m.d.x);
-      put(m, 1, (uint32_t)m.d.y);
-    }
+// ------------------------------------------------------------------ 6-wide traversal tree
+// Which binary nodes become 6-wide nodes depends on the path from the root
+// (a wide node's internal children do), but the children a binary node would
+// have as a wide node depend on its own subtree alone.  So k_cut finds every
+// binary node's six children at once (its "cut"), and tells each internal one
+// from which distance up it belongs to a cut; k_wide_roots then settles by a walk
+// to the root which nodes are reached.  A level-by-level pass from the root would
+// visit fewer nodes but needs a launch per level.
+constexpr int CUT_T = 256;
+
+__device__ __forceinline__ bool better_area(float a, float best) { return !(a <= best); }  // NaN counts as largest
+
+// cut[6 n ..]: node n's children as a wide node, in the order the wide node
+// stores them (ascending box centre along `axis`; unused slots DT_NO_CHILD).
+// member[c] bit d (1..5): c belongs to the cut of its d-th ancestor; bits 8-9:
+// c's own cut's axis.
+__global__ void __launch_bounds__(CUT_T) k_cut(int32_t n_int, const BvhNode* nodes, uint32_t* cut, int32_t* member) {
+  const int i = blockIdx.x * CUT_T + threadIdx.x;
+  if (i >= n_int) return;
+  uint32_t c[DT_WIDE];
+  TBox b[DT_WIDE];
+  int dist[DT_WIDE];
+  {
+    const BvhNode n = nodes[i];
+    c[0] = (uint32_t)n.d.x;
+    c[1] = (uint32_t)n.d.y;
+    b[0] = get_box(n, 0);
+    b[1] = get_box(n, 1);
+    dist[0] = dist[1] = 1;
   }
-  int cnt = k;
-  for (; k < 4; ++k) {
-    lo[k][0] = lo[k][1] = lo[k][2] = 0.f;
-    hi[k][0] = hi[k][1] = hi[k][2] = 0.f;
-    ch[k] = DT_NO_CHILD;
+#pragma unroll
+  for (int k = 2; k < DT_WIDE; ++k) {
+    c[k] = DT_NO_CHILD;
+    b[k] = {mk3(0.f, 0.f, 0.f), mk3(0.f, 0.f, 0.f)};
+    dist[k] = 0;
   }
-  Bvh4Node q;
+  int cnt = 2;
+#pragma unroll
+  for (int step = 0; step < DT_WIDE - 2; ++step) {
+    // the internal child of largest area is replaced by its two children
+    int bi = -1, bd = 0;
+    uint32_t bc = 0u;
+    float best = -1.f;
+#pragma unroll
+    for (int k = 0; k < step + 2; ++k) {
+      if (c[k] & DT_LEAF_BIT) continue;
+      const float a = tarea(b[k]);
+      if (better_area(a, best)) {
+        best = a;
+        bi = k;
+        bc = c[k];
+        bd = dist[k];
+      }
+    }
+    if (bi < 0 || bc >= (uint32_t)n_int) break;
+    const BvhNode n = nodes[bc];
+    const TBox b0 = get_box(n, 0);
+#pragma unroll
+    for (int k = 0; k < step + 2; ++k)
+      if (k == bi) {
+        c[k] = (uint32_t)n.d.x;
+        b[k] = b0;
+        dist[k] = bd + 1;
+      }
+    c[step + 2] = (uint32_t)n.d.y;
+    b[step + 2] = get_box(n, 1);
+    dist[step + 2] = bd + 1;
+    cnt = step + 3;
+  }
+  // the axis the (doubled) box centres spread most along
+  v3 mean = mk3(0.f, 0.f, 0.f), sq = mean;
+#pragma unroll
+  for (int k = 0; k < DT_WIDE; ++k)
+    if (k < cnt) {
+      const v3 m = b[k].lo + b[k].hi;
+      mean += m;
+      sq += mk3(m.x * m.x, m.y * m.y, m.z * m.z);
+    }
+  const float f = 1.f / (float)cnt;
+  const v3 var = mk3(sq.x - mean.x * mean.x * f, sq.y - mean.y * mean.y * f, sq.z - mean.z * mean.z * f);
+  const int axis = var.x >= var.y ? (var.x >= var.z ? 0 : 2) : (var.y >= var.z ? 1 : 2);
+  int key[DT_WIDE];
+#pragma unroll
+  for (int k = 0; k < DT_WIDE; ++k) key[k] = fenc(comp(b[k].lo, axis) + comp(b[k].hi, axis));
+#pragma unroll
+  for (int k = 0; k < DT_WIDE; ++k) {
+    int rank = k;  // unused slots stay last
+    if (k < cnt) {
+      rank = 0;
+#pragma unroll
+      for (int j = 0; j < DT_WIDE; ++j)
+        if (j < cnt && j != k) rank += key[j] < key[k] || (key[j] == key[k] && j < k) ? 1 : 0;
+      if (!(c[k] & DT_LEAF_BIT) && c[k] < (uint32_t)n_int) atomicOr(&member[c[k]], 1 << dist[k]);
+    }
+    cut[(size_t)DT_WIDE * i + rank] = c[k];
+  }
+  if (axis) atomicOr(&member[i], axis << 8);
+}
+
+__device__ __forceinline__ int block_max(int v) {
+  __shared__ int sh[CUT_T / 64];
+  for (int s = 32; s > 0; s >>= 1) v = max(v, __shfl_xor(v, s, 64));
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  for (int k = 0; k < CUT_T / 64; ++k) v = max(v, sh[k]);
+  return v;
+}
+
+// cnt[n] = (internal | leaf << 32) children of the wide node n becomes, 0 where
+// it becomes none.  Node n does if it is the root or belongs to the cut of an
+// ancestor that does; walking up, bit h of w says "n is one if the ancestor h
+// levels above the current one is".  Also the binary tree's height (root = 1).
+__global__ void __launch_bounds__(CUT_T) k_wide_roots(int32_t n_int, const BvhNode* nodes, const uint32_t* cut,
+                                                      const int32_t* member, unsigned long long* cnt,
+                                                      BvhHeader* hdr) {
+  const int i = blockIdx.x * CUT_T + threadIdx.x;
+  int dep = 0;
+  if (i < n_int) {
+    uint32_t w = 1u;
+    int p = i;
+    while (p > 0 && p < n_int && dep < 4096) {
+      if (w & 1u) w |= (uint32_t)member[p] & 0x3Eu;
+      w >>= 1;
+      p = nodes[p].d.z;
+      ++dep;
+    }
+    unsigned long long v = 0ull;
+    if (w & 1u) {
+      uint32_t ni = 0, nl = 0;
+#pragma unroll
+      for (int k = 0; k < DT_WIDE; ++k) {
+        const uint32_t r = cut[(size_t)DT_WIDE * i + k];
+        if (r == DT_NO_CHILD) continue;
+        ni += (r & DT_LEAF_BIT) ? 0u : 1u;
+        nl += (r & DT_LEAF_BIT) ? 1u : 0u;
+      }
+      v = (unsigned long long)ni | ((unsigned long long)nl << 32);
+    }
+    cnt[i] = v;
+    dep += 2;  // the deepest internal node has a leaf child one level below it
+  }
+  dep = block_max(dep);
+  if (threadIdx.x == 0) atomicMax(&hdr->depth, dep);
+}
+
+// owner[w]: the binary node of wide node w.  The root is wide node 0; the
+// internal children of binary node i's wide node are 1 + pre[i] (low) onwards
+__global__ void k_wide_owner(int32_t n_int, const uint32_t* cut, const unsigned long long* cnt,
+                             const unsigned long long* pre, int32_t* owner, int32_t cap) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n_int || cnt[i] == 0ull) return;
+  if (i == 0) owner[0] = 0;
+  uint32_t at = 1u + (uint32_t)pre[i];
+#pragma unroll
+  for (int k = 0; k < DT_WIDE; ++k) {
+    const uint32_t r = cut[(size_t)DT_WIDE * i + k];
+    if (r & DT_LEAF_BIT) continue;  // DT_NO_CHILD has the bit too
+    if (at < (uint32_t)cap) owner[at] = (int32_t)r;
+    ++at;
+  }
+}
+
+// Writes wide node w and its leaves: a group of 8 lanes per node, one child
+// each (a node per lane leaves most of the chip waiting for one lane's chain
+// of child loads).  total: the scan's grand total (low: wide nodes but the
+// root).
+__global__ void __launch_bounds__(CUT_T) k_wide_write(const float* V, const int32_t* F, int32_t nv, int32_t nf,
+                                                      const int32_t* sorted, const BvhNode* nodes,
+                                                      const uint32_t* cut, const int32_t* member,
+                                                      const unsigned long long* pre,
+                                                      const unsigned long long* total, const int32_t* owner,
+                                                      WideNode* out, int32_t cap, float4* leaves) {
+  const int n_int = nf - 1;
+  const uint32_t count = min(1u + (uint32_t)*total, (uint32_t)cap);
+  const uint32_t w = (uint32_t)((blockIdx.x * (int64_t)CUT_T + threadIdx.x) >> 3);
+  const int sub = threadIdx.x & 7, lane = threadIdx.x & 63;
+  const bool live = w < count;
+  int n = live ? owner[w] : 0;
+  n = n < 0 || n >= n_int ? 0 : n;
+  const uint32_t ref = live && sub < DT_WIDE ? cut[(size_t)DT_WIDE * n + sub] : DT_NO_CHILD;
+  const bool valid = ref != DT_NO_CHILD;
+  const bool is_leaf = valid && (ref & DT_LEAF_BIT) != 0u, is_int = valid && !is_leaf;
+  const uint32_t im = (uint32_t)(__ballot(is_int) >> (lane & ~7)) & 0x3Fu;
+  const uint32_t lmask = (uint32_t)(__ballot(is_leaf) >> (lane & ~7)) & 0x3Fu;
+  const unsigned long long base = live ? pre[n] : 0ull;
+  const uint32_t child_base = 1u + (uint32_t)base, leaf_base = (uint32_t)(base >> 32);
+  TBox box = {mk3(INFINITY, INFINITY, INFINITY), mk3(-INFINITY, -INFINITY, -INFINITY)};
+  if (is_leaf) {
+    const uint32_t j = min(ref & ~DT_LEAF_BIT, (uint32_t)(nf - 1));
+    const int f = sorted[j];
+    const v3 a = load3(V + 3 * vclamp(F[3 * f], nv)), b = load3(V + 3 * vclamp(F[3 * f + 1], nv));
+    const v3 c = load3(V + 3 * vclamp(F[3 * f + 2], nv));
+    box = {vmin(vmin(a, b), c), vmax(vmax(a, b), c)};
+    const size_t q = leaf_base + (uint32_t)__popc(lmask & ((1u << sub) - 1u));
+    if (q < (size_t)nf) {
+      leaves[3 * q] = make_float4(a.x, a.y, a.z, __int_as_float(f));
+      leaves[3 * q + 1] = make_float4(b.x, b.y, b.z, 0.f);
+      leaves[3 * q + 2] = make_float4(c.x, c.y, c.z, 0.f);
+    }
+  } else if (is_int && ref < (uint32_t)n_int) {
+    const BvhNode m = nodes[ref];
+    box = tunion(get_box(m, 0), get_box(m, 1));
+  }
   float org[3];
-  uint32_t ebits = 0, qlo[3] = {0u, 0u, 0u}, qhi[3] = {0u, 0u, 0u};
+  uint32_t ebits = 0, qlo[3], qhi[3];
+#pragma unroll
   for (int a = 0; a < 3; ++a) {
-    float nlo = lo[0][a], nhi = hi[0][a];
-    for (int c = 1; c < cnt; ++c) {
-      nlo = fminf(nlo, lo[c][a]);
-      nhi = fmaxf(nhi, hi[c][a]);
+    const float lo = comp(box.lo, a), hi = comp(box.hi, a);
+    float nlo = lo, nhi = hi;
+#pragma unroll
+    for (int s = 1; s < 8; s <<= 1) {
+      nlo = fminf(nlo, __shfl_xor(nlo, s));
+      nhi = fmaxf(nhi, __shfl_xor(nhi, s));
     }
-    int e = quant_exponent(nlo, nhi);
-    float sc = ldexpf(1.0f, e);
-    float p = floorf(ldexpf(nlo, -e)) * sc;  // a multiple of sc, <= nlo
+    const int e = quant_exponent(nlo, nhi);
+    const float sc = ldexpf(1.0f, e);
+    const float p = floorf(ldexpf(nlo, -e)) * sc;  // a multiple of sc, <= nlo
     org[a] = p;
     ebits |= (uint32_t)(uint8_t)(int8_t)e << (8 * a);
-    for (int c = 0; c < cnt; ++c) {
-      int ql = (int)floorf(ldexpf(lo[c][a] - p, -e));
+    int ql = 255, qh = 0;  // an unused slot's box is inverted: never entered
+    if (valid) {
+      ql = (int)floorf(ldexpf(lo - p, -e));
       ql = ql < 0 ? 0 : (ql > 255 ? 255 : ql);
-      while (ql > 0 && p + (float)ql * sc > lo[c][a]) --ql;
-      int qh = (int)ceilf(ldexpf(hi[c][a] - p, -e));
+      while (ql > 0 && p + (float)ql * sc > lo) --ql;
+      qh = (int)ceilf(ldexpf(hi - p, -e));
       qh = qh < 0 ? 0 : (qh > 255 ? 255 : qh);
-      while (qh < 255 && p + (float)qh * sc < hi[c][a]) ++qh;
-      qlo[a] |= (uint32_t)ql << (8 * c);
-      qhi[a] |= (uint32_t)qh << (8 * c);
+      while (qh < 255 && p + (float)qh * sc < hi) ++qh;
+    }
+    qlo[a] = (uint32_t)ql;
+    qhi[a] = (uint32_t)qh;
+  }
+  // the packed step words: children 0-3 one byte each, 4 and 5 with both bounds
+  uint32_t lo4[3], hi4[3], q45[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    lo4[a] = sub < 4 ? qlo[a] << (8 * sub) : 0u;
+    hi4[a] = sub < 4 ? qhi[a] << (8 * sub) : 0u;
+    q45[a] = sub == 4 || sub == 5 ? (qlo[a] << (8 * (sub - 4))) | (qhi[a] << (8 * (sub - 2))) : 0u;
+#pragma unroll
+    for (int s = 1; s < 8; s <<= 1) {
+      lo4[a] |= (uint32_t)__shfl_xor((int)lo4[a], s);
+      hi4[a] |= (uint32_t)__shfl_xor((int)hi4[a], s);
+      q45[a] |= (uint32_t)__shfl_xor((int)q45[a], s);
     }
   }
-  q.org = make_float4(org[0], org[1], org[2], __uint_as_float(ebits | ((uint32_t)cnt << 24)));
-  q.qlo = make_uint4(qlo[0], qlo[1], qlo[2], 0u);
-  q.qhi = make_uint4(qhi[0], qhi[1], qhi[2], 0u);
-  q.child = make_uint4(ch[0], ch[1], ch[2], ch[3]);
-  out[j] = q;
+  if (!live || sub > 3) return;
+  const uint32_t axis = ((uint32_t)member[n] >> 8) & 3u;
+  uint4 v = make_uint4(__float_as_uint(org[0]), __float_as_uint(org[1]), __float_as_uint(org[2]),
+                       ebits | (im << 24) | (axis << 30));
+  if (sub == 1) v = make_uint4((child_base & DT_WIDE_INDEX) | (lmask << 26), leaf_base, lo4[0], hi4[0]);
+  if (sub == 2) v = make_uint4(lo4[1], hi4[1], lo4[2], hi4[2]);
+  if (sub == 3) v = make_uint4(q45[0], q45[1], q45[2], 0u);
+  ((uint4*)(out + w))[sub] = v;
 }
 
 __global__ void k_header(BvhHeader* hdr, int32_t nv, int32_t nf) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     hdr->nv = nv;
     hdr->nf = nf;
-    hdr->depth = nf == 1 ? 1 : 0;  // larger trees: the last depth-parity pass
+    hdr->depth = nf == 1 ? 1 : 0;  // larger trees: k_wide_roots
     hdr->pad0 = 0;
   }
 }
@@ -718,7 +903,7 @@ struct BuildWs {
   float* bpart;
   int32_t* arrive;
   int* acc;
-  int32_t *flag4, *idx4;
+  int32_t *flag, *member;
   int32_t *vcnt, *cursor;
 };
 
@@ -736,8 +921,8 @@ size_t carve_build(Carver& c, int32_t nv, int32_t nf, BuildWs* w) {
   x.bpart = c.take<float>(NBB * 6);
   x.arrive = c.take<int32_t>(nf > 1 ? nf - 1 : 1);
   x.acc = c.take<int>(6 * (size_t)(nf > 1 ? nf - 1 : 1));
-  x.flag4 = c.take<int32_t>(nf);
-  x.idx4 = c.take<int32_t>(nf);
+  x.flag = c.take<int32_t>(nf);
+  x.member = c.take<int32_t>(nf);
   x.vcnt = c.take<int32_t>(nv);
   x.cursor = c.take<int32_t>(nv);
   if (w) *w = x;
@@ -760,15 +945,20 @@ size_t dt_scan_partials_count() { return SCAN_NB + 1; }
 
 // out[0..n) = exclusive prefix sums of in[0..n); partials[SCAN_NB] = total.
 // in == out is allowed.
-dt_status dt_scan_exclusive_i32(const int32_t* in, int32_t* out, int32_t n, int32_t* partials,
-                                hipStream_t s) {
+template <class T>
+static dt_status scan_exclusive(const T* in, T* out, int32_t n, T* partials, hipStream_t s) {
   if (n <= 0) return DT_OK;
   int32_t chunk = (n + SCAN_NB - 1) / SCAN_NB;
-  hipLaunchKernelGGL(k_scan_reduce, dim3(SCAN_NB), dim3(SCAN_T), 0, s, in, n, chunk, partials);
-  hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(SCAN_NB), 0, s, partials, SCAN_NB);
-  hipLaunchKernelGGL(k_scan_apply, dim3(SCAN_NB), dim3(SCAN_T), 0, s, in, out, n, chunk, partials);
+  hipLaunchKernelGGL(k_scan_reduce<T>, dim3(SCAN_NB), dim3(SCAN_T), 0, s, in, n, chunk, partials);
+  hipLaunchKernelGGL(k_scan_partials<T>, dim3(1), dim3(SCAN_NB), 0, s, partials, SCAN_NB);
+  hipLaunchKernelGGL(k_scan_apply<T>, dim3(SCAN_NB), dim3(SCAN_T), 0, s, in, out, n, chunk, partials);
   DT_CHECK_LAUNCH();
   return DT_OK;
+}
+
+dt_status dt_scan_exclusive_i32(const int32_t* in, int32_t* out, int32_t n, int32_t* partials,
+                                hipStream_t s) {
+  return scan_exclusive(in, out, n, partials, s);
 }
 
 // ------------------------------------------------------------------ C ABI
@@ -853,31 +1043,37 @@ extern "C" dt_status dt_build_bvh(const float* V, int32_t nv, const int32_t* F, 
   // tree + boxes
   if (nf > 1) {
     hipLaunchKernelGGL(k_karras, dim3(dt_blocks(nf - 1, 256)), dim3(256), 0, s, ki, nf, nodes, lpar);
-    if (dt_status st = dt_fill_u32((uint32_t*)w.arrive, 0u, nf - 1, s)) return st;
     hipLaunchKernelGGL(k_fit_init, dim3(dt_blocks(6 * (int64_t)(nf - 1), 256) < 4096 ?
                                         dt_blocks(6 * (int64_t)(nf - 1), 256) : 4096),
-                       dim3(256), 0, s, w.acc, nf - 1);
+                       dim3(256), 0, s, w.acc, w.arrive, w.member, nf - 1);
   }
   hipLaunchKernelGGL(k_fit, dim3(dt_blocks(nf, 256)), dim3(256), 0, s, V, F, nv, vi, nf, nodes,
                      lpar, w.arrive, w.acc, leaves);
   // treelet restructuring: even-depth roots, then odd, twice
   if (nf > 2) {
     for (int pass = 0; pass < TREELET_PASSES; ++pass) {
-      hipLaunchKernelGGL(k_even, dim3(dt_blocks(nf - 1, 256)), dim3(256), 0, s, nf - 1, nodes, w.flag4,
-                         (BvhHeader*)nullptr);
+      hipLaunchKernelGGL(k_even, dim3(dt_blocks(nf - 1, 256)), dim3(256), 0, s, nf - 1, nodes, w.flag);
       hipLaunchKernelGGL(k_treelet, dim3(dt_blocks(nf - 1, 256)), dim3(256), 0, s, nf - 1, nodes, lpar,
-                         w.flag4, (pass & 1) == 0 ? 1 : 0);
+                         w.flag, (pass & 1) == 0 ? 1 : 0);
     }
   }
   DT_CHECK_LAUNCH();
-  // 4-wide traversal tree
+  // 6-wide traversal tree.  The box accumulators, the sort's key buffers and the
+  // parity flags are free by now and hold the cuts, the child counts with
+  // their prefix sums, and the wide nodes' owners
   if (nf > 1) {
-    Bvh4Node* nodes4 = (Bvh4Node*)(b + L.nodes4);
-    hipLaunchKernelGGL(k_even, dim3(dt_blocks(nf - 1, 256)), dim3(256), 0, s, nf - 1, nodes, w.flag4,
-                       hdr);
-    if (dt_status st = dt_scan_exclusive_i32(w.flag4, w.idx4, nf - 1, w.scanp, s)) return st;
-    hipLaunchKernelGGL(k_collapse, dim3(dt_blocks(nf - 1, 256)), dim3(256), 0, s, nf - 1, nodes,
-                       w.flag4, w.idx4, nodes4, bvh4_cap(nf));
+    uint32_t* cut = (uint32_t*)w.acc;
+    unsigned long long *cnt = (unsigned long long*)w.k0, *pre = (unsigned long long*)w.k1;
+    unsigned long long* part = (unsigned long long*)w.bpart;  // SCAN_NB + 1 sums
+    static_assert(NBB * 6 * sizeof(float) >= (SCAN_NB + 1) * sizeof(unsigned long long), "scan partials");
+    const int32_t cap = wide_cap(nf);
+    const unsigned nb = dt_blocks(nf - 1, CUT_T);
+    hipLaunchKernelGGL(k_cut, dim3(nb), dim3(CUT_T), 0, s, nf - 1, nodes, cut, w.member);
+    hipLaunchKernelGGL(k_wide_roots, dim3(nb), dim3(CUT_T), 0, s, nf - 1, nodes, cut, w.member, cnt, hdr);
+    if (dt_status st = scan_exclusive(cnt, pre, nf - 1, part, s)) return st;
+    hipLaunchKernelGGL(k_wide_owner, dim3(nb), dim3(CUT_T), 0, s, nf - 1, cut, cnt, pre, w.flag, cap);
+    hipLaunchKernelGGL(k_wide_write, dim3(dt_blocks(8 * (int64_t)cap, CUT_T)), dim3(CUT_T), 0, s, V, F, nv, nf, vi,
+                       nodes, cut, w.member, pre, part + SCAN_NB, w.flag, (WideNode*)(b + L.wide), cap, leaves);
     DT_CHECK_LAUNCH();
   }
   return DT_OK;

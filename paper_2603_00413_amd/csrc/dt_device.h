@@ -249,24 +249,27 @@ __device__ __forceinline__ bool tri_test(const RayPre& r, v3 a, v3 b, v3 c, int 
 #define DT_STACK 64       // total stack entries per lane (LDS part + global overflow part)
 #define DT_STACK_LDS 8    // entries kept in LDS by the traversal kernels (4 KB per wave)
 
-// Closest-hit traversal of the 4-wide tree as a resumable per-lane state,
-// advanced one node at a time.  The stack holds (node, entry distance) pairs:
-// the first SL entries in LDS (stk points at this lane's column, stride
-// entries apart), deeper ones in this lane's global overflow area gstk (gcap
-// entries; may be NULL when GLOBAL is false).  At a node, the leaf children
-// whose boxes the ray enters are handed back for testing; the internal ones
-// are ordered by entry distance, the nearest is visited next and the others
-// are pushed, farthest first.  A popped subtree whose box is entered beyond
-// the closest hit known when it is popped is skipped without fetching its
-// node.  overflow is set if the stack would overflow (the result is then
+// Closest-hit traversal of the 6-wide tree as a per-lane state, advanced one
+// node at a time.  A visit tests the six child boxes and gets a 6-bit mask of
+// the entered ones; the leaves among them are handed back for testing, and of
+// the internal ones the first in the node's order for this ray's direction is
+// visited next.  The others stay together as one stack entry (child_base |
+// remaining mask << 26, imask | reversed << 8), so a visit pushes at most one
+// entry and orders nothing, where sorting the children by entry distance and
+// pushing each with its distance took a third of the instructions; the axis
+// order costs 2-3 % more visits than the exact one.  The first SL entries live
+// in LDS (stk points at this lane's column, stride entries apart), deeper ones
+// in this lane's overflow area gstk (gcap entries; may be NULL when GLOBAL is
+// false).  overflow is set if the stack would overflow (the result is then
 // incomplete and flagged).
 struct Trav {
   RayPre r;
   Hit h;
+  v3 slack;        // per axis: the slab distances' error bound (trav_init)
   uint32_t node;
+  uint32_t neg;    // bit per axis: the direction's component is negative
   int sp;
   int skip;
-  uint32_t steps;
   bool overflow;
   bool done;
 };
@@ -280,142 +283,130 @@ __device__ __forceinline__ void trav_init(Trav& s, const BvhView& bv, v3 o, v3 d
   s.node = 0;
   s.sp = 0;
   s.skip = skip;
-  s.steps = 0;
   s.overflow = false;
   s.done = false;
+  s.neg = (s.r.inv.x < 0.f ? 1u : 0u) | (s.r.inv.y < 0.f ? 2u : 0u) | (s.r.inv.z < 0.f ? 4u : 0u);
+  s.slack = mk3(0.f, 0.f, 0.f);
   if (bv.nf == 1) {
     const float4* L = bv.leaves;
     int f = __float_as_int(L[0].w);
     if (f != skip) tri_test(s.r, xyz(L[0]), xyz(L[1]), xyz(L[2]), f, t_eps, s.h);
     s.done = true;
+    return;
   }
+  // Slab distances are taken straight from the codes: the plane p + q s lies
+  // at t(q) = (p + q s - o) inv = q a + b, a = s inv (exact, s is a power of
+  // two) and b = (p - o) inv, one fused multiply-add per plane.  Against the
+  // exact (p + q s - o) / d the computed value is off by at most about
+  // 6u (255 |a| + |b|), u = 2^-24 (the roundings of p - o, of inv and of the
+  // two fused multiply-adds).  Every node lies in the root's box [p0, p0 +
+  // 255 s0] and a step is at most 2/254 of its node's extent (or at most the
+  // root's step), so 255 s + |p - o| <= |p0 - o| + 4 * 255 s0 for every node:
+  // near planes are lowered and far planes raised by slack = 8u (|p0 - o| +
+  // 4 * 255 s0) |inv|, so near and far distances bound the exact ones from
+  // below and above and no box the exact ray enters before the closest hit is
+  // rejected.
+  const float4 org = bv.wide[0].org;
+  const uint32_t eb = __float_as_uint(org.w);
+  auto bound = [](float p, float o, float inv, int e) {
+    return 0x1p-21f * (fabsf(p - o) + 1020.f * ldexpf(1.f, e)) * fabsf(inv);
+  };
+  s.slack = mk3(bound(org.x, o.x, s.r.inv.x, (int)(int8_t)(eb & 0xFFu)),
+                bound(org.y, o.y, s.r.inv.y, (int)(int8_t)((eb >> 8) & 0xFFu)),
+                bound(org.z, o.z, s.r.inv.z, (int)(int8_t)((eb >> 16) & 0xFFu)));
 }
 
 // One step: visit the current node and choose the next one (or finish).
-// Bit k of lm is set for each leaf child k whose box the ray enters, with its
-// leaf index in lf[k]; those are left to the caller to test.
+// lm: the leaf children whose boxes the ray enters, left to the caller to
+// test; their leaf indices are lbase plus the number of bits of lall below.
 template <int SL, bool GLOBAL>
 __device__ __forceinline__ void trav_visit(Trav& s, const BvhView& bv, uint2* stk, int stride,
-                                           uint2* gstk, int gcap, uint32_t& lm, uint32_t* lf) {
-  const uint32_t cap4 = (uint32_t)bvh4_cap(bv.nf);
-  const uint32_t lmax = (uint32_t)(bv.nf - 1);
-  // a depth-first walk visits each 4-wide node at most once
-  if (s.node >= cap4 || ++s.steps > cap4 + 64) {
+                                           uint2* gstk, int gcap, uint32_t& lm, uint32_t& lall,
+                                           uint32_t& lbase) {
+  if (s.node >= (uint32_t)wide_cap(bv.nf)) {
     s.overflow = true;
     s.done = true;
     return;
   }
-  auto push = [&](uint32_t c, float t) {
-    uint2 e = make_uint2(c, __float_as_uint(t));
+  const WideNode& n = bv.wide[s.node];
+  const float4 org = n.org;
+  const uint4 A = n.a, B = n.b, C = n.c;
+  const uint32_t eb = __float_as_uint(org.w);
+  const float ax = ldexpf(s.r.inv.x, (int)(int8_t)(eb & 0xFFu));
+  const float ay = ldexpf(s.r.inv.y, (int)(int8_t)((eb >> 8) & 0xFFu));
+  const float az = ldexpf(s.r.inv.z, (int)(int8_t)((eb >> 16) & 0xFFu));
+  const float ox = org.x - s.r.o.x, oy = org.y - s.r.o.y, oz = org.z - s.r.o.z;
+  const float bnx = fmaf(ox, s.r.inv.x, -s.slack.x), bfx = fmaf(ox, s.r.inv.x, s.slack.x);
+  const float bny = fmaf(oy, s.r.inv.y, -s.slack.y), bfy = fmaf(oy, s.r.inv.y, s.slack.y);
+  const float bnz = fmaf(oz, s.r.inv.z, -s.slack.z), bfz = fmaf(oz, s.r.inv.z, s.slack.z);
+  // the near face per axis follows the sign of inv
+  const bool px = !(s.r.inv.x < 0.f), py = !(s.r.inv.y < 0.f), pz = !(s.r.inv.z < 0.f);
+  const uint32_t nqx = px ? A.z : A.w, fqx = px ? A.w : A.z;
+  const uint32_t nqy = py ? B.x : B.y, fqy = py ? B.y : B.x;
+  const uint32_t nqz = pz ? B.z : B.w, fqz = pz ? B.w : B.z;
+  const uint32_t x45 = px ? C.x : (C.x >> 16) | (C.x << 16);
+  const uint32_t y45 = py ? C.y : (C.y >> 16) | (C.y << 16);
+  const uint32_t z45 = pz ? C.z : (C.z >> 16) | (C.z << 16);
+  // widened like the exit distances (the closest hit's t carries rounding
+  // too, and boxes entered at exactly that t must stay in play for ties)
+  const float tmaxw = s.h.t * 1.0000008f;
+  uint32_t hit = 0;
+#pragma unroll
+  for (int k = 0; k < DT_WIDE; ++k) {
+    const int sh = 8 * (k & 3);
+    const uint32_t wx = k < 4 ? nqx : x45, wy = k < 4 ? nqy : y45, wz = k < 4 ? nqz : z45;
+    const uint32_t vx = k < 4 ? fqx : x45 >> 16, vy = k < 4 ? fqy : y45 >> 16, vz = k < 4 ? fqz : z45 >> 16;
+    const float tnx = fmaf((float)((wx >> sh) & 0xFFu), ax, bnx);
+    const float tny = fmaf((float)((wy >> sh) & 0xFFu), ay, bny);
+    const float tnz = fmaf((float)((wz >> sh) & 0xFFu), az, bnz);
+    const float tfx = fmaf((float)((vx >> sh) & 0xFFu), ax, bfx);
+    const float tfy = fmaf((float)((vy >> sh) & 0xFFu), ay, bfy);
+    const float tfz = fmaf((float)((vz >> sh) & 0xFFu), az, bfz);
+    const float tn = fmaxf(fmaxf(tnx, tny), fmaxf(tnz, 0.0f));
+    const float tf = fminf(fminf(tfx, tfy), fminf(tfz, tmaxw));
+    hit |= tn <= tf ? 1u << k : 0u;
+  }
+  const uint32_t im = (eb >> 24) & 0x3Fu;
+  lall = A.x >> 26;
+  lbase = A.y;
+  lm = hit & lall;
+  // the group to go on with: this node's entered internal children, or the
+  // last group on the stack
+  const uint32_t ih = hit & im;
+  uint2 g = make_uint2((A.x & DT_WIDE_INDEX) | (ih << 26), im | (((s.neg >> (eb >> 30)) & 1u) << 8));
+  if (ih == 0u) {
+    if (s.sp == 0) {
+      s.done = true;
+      return;
+    }
+    --s.sp;
     if (s.sp < SL) {
-      stk[s.sp * stride] = e;
+      g = stk[s.sp * stride];
+    } else {
+      if constexpr (GLOBAL) g = gstk[s.sp - SL];
+    }
+  }
+  const uint32_t m = g.x >> 26;
+  const uint32_t bit = (g.y & 256u) ? 0x80000000u >> __clz((int)m) : m & (0u - m);
+  s.node = (g.x & DT_WIDE_INDEX) + (uint32_t)__popc(g.y & 0x3Fu & (bit - 1u));
+  if (m != bit) {
+    g.x &= ~(bit << 26);
+    if (s.sp < SL) {
+      stk[s.sp * stride] = g;
       ++s.sp;
     } else if (GLOBAL && s.sp - SL < gcap) {
-      if constexpr (GLOBAL) gstk[s.sp - SL] = e;
+      if constexpr (GLOBAL) gstk[s.sp - SL] = g;
       ++s.sp;
     } else {
       s.overflow = true;
     }
-  };
-  const Bvh4Node& n = bv.nodes4[s.node];
-  const float4 org = n.org;
-  const uint4 ql = n.qlo, qh = n.qhi, cc = n.child;
-  // the quantized child boxes: lo = p + qlo s, hi = p + qhi s, s = 2^e per axis
-  const uint32_t eb = __float_as_uint(org.w);
-  const int ebx = (int)(int8_t)(eb & 0xFFu), eby = (int)(int8_t)((eb >> 8) & 0xFFu);
-  const int ebz = (int)(int8_t)((eb >> 16) & 0xFFu);
-  // widened like the exit distances (the closest hit's t carries rounding
-  // too, and boxes entered at exactly that t must stay in play for ties)
-  const float tmaxw = (s.h.tri >= 0 ? s.h.t : INFINITY) * 1.0000008f;
-  // Slab distances straight from the codes: the plane p + q s lies at
-  // t(q) = (p + q s - o) inv = q a + b with a = s inv (exact, s is a power of
-  // two) and b = (p - o) inv, one fused multiply-add per plane.  Against the
-  // exact (p + q s - o) / d the computed value is off by at most about
-  // 6u (255 |a| + |b|), u = 2^-24 (the roundings of b, of inv, of the fma);
-  // each axis's near planes are lowered and far planes raised by
-  // 8u (255 |a| + |b|), so near and far distances bound the exact ones from
-  // below and above and no box the exact ray enters before the closest hit is
-  // rejected.  The near face per axis follows the sign of inv.
-  const float ax = ldexpf(s.r.inv.x, ebx), ay = ldexpf(s.r.inv.y, eby), az = ldexpf(s.r.inv.z, ebz);
-  const float bx = (org.x - s.r.o.x) * s.r.inv.x;
-  const float by = (org.y - s.r.o.y) * s.r.inv.y;
-  const float bz = (org.z - s.r.o.z) * s.r.inv.z;
-  const float ex = 0x1p-21f * fmaf(255.f, fabsf(ax), fabsf(bx));
-  const float ey = 0x1p-21f * fmaf(255.f, fabsf(ay), fabsf(by));
-  const float ez = 0x1p-21f * fmaf(255.f, fabsf(az), fabsf(bz));
-  const float bnx = bx - ex, bfx = bx + ex, bny = by - ey, bfy = by + ey, bnz = bz - ez, bfz = bz + ez;
-  const bool px = s.r.inv.x >= 0.f, py = s.r.inv.y >= 0.f, pz = s.r.inv.z >= 0.f;
-  const uint32_t nqx = px ? ql.x : qh.x, fqx = px ? qh.x : ql.x;
-  const uint32_t nqy = py ? ql.y : qh.y, fqy = py ? qh.y : ql.y;
-  const uint32_t nqz = pz ? ql.z : qh.z, fqz = pz ? qh.z : ql.z;
-  float t[4];
-  uint32_t c[4] = {cc.x, cc.y, cc.z, cc.w};
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int sh = 8 * k;
-    const float tnx = fmaf((float)((nqx >> sh) & 0xFFu), ax, bnx);
-    const float tny = fmaf((float)((nqy >> sh) & 0xFFu), ay, bny);
-    const float tnz = fmaf((float)((nqz >> sh) & 0xFFu), az, bnz);
-    const float tfx = fmaf((float)((fqx >> sh) & 0xFFu), ax, bfx);
-    const float tfy = fmaf((float)((fqy >> sh) & 0xFFu), ay, bfy);
-    const float tfz = fmaf((float)((fqz >> sh) & 0xFFu), az, bfz);
-    const float tn = fmaxf(fmaxf(tnx, tny), fmaxf(tnz, 0.0f));
-    const float tf = fminf(fminf(tfx, tfy), fminf(tfz, tmaxw));
-    t[k] = tn <= tf ? tn : INFINITY;
   }
-  // branch-free split of the entered children into leaves and internal nodes
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const bool entered = c[k] != DT_NO_CHILD && t[k] != INFINITY;
-    const bool is_leaf = entered && (c[k] & DT_LEAF_BIT) != 0u;
-    lf[k] = min(c[k] & ~DT_LEAF_BIT, lmax);
-    lm |= is_leaf ? (1u << k) : 0u;
-    t[k] = entered && !is_leaf ? t[k] : INFINITY;
-  }
-  // order the entered internal children by entry distance (sorting network)
-#define DT_CSWAP(i, j)                 \
-  if (t[j] < t[i]) {                   \
-    float tt = t[i];                   \
-    t[i] = t[j];                       \
-    t[j] = tt;                         \
-    uint32_t cx = c[i];                \
-    c[i] = c[j];                       \
-    c[j] = cx;                         \
-  }
-  DT_CSWAP(0, 1)
-  DT_CSWAP(2, 3)
-  DT_CSWAP(0, 2)
-  DT_CSWAP(1, 3)
-  DT_CSWAP(1, 2)
-#undef DT_CSWAP
-  if (t[0] != INFINITY) {
-    if (t[3] != INFINITY) push(c[3], t[3]);
-    if (t[2] != INFINITY) push(c[2], t[2]);
-    if (t[1] != INFINITY) push(c[1], t[1]);
-    s.node = c[0];
-    return;
-  }
-  // pop the nearest pending subtree that can still hold a closer hit
-  // (the margin keeps equal-distance ties, decided by triangle id, in play)
-  while (s.sp > 0) {
-    --s.sp;
-    uint2 e = make_uint2(0u, 0u);
-    if (s.sp < SL) {
-      e = stk[s.sp * stride];
-    } else {
-      if constexpr (GLOBAL) e = gstk[s.sp - SL];
-    }
-    if (s.h.tri >= 0 && __uint_as_float(e.y) > s.h.t * 1.000001f) continue;
-    s.node = e.x;
-    return;
-  }
-  s.done = true;
 }
 
 // Closest hits of a wave's 64 rays, leaf tests batched across the wave.
 //
 // A lane's ray visits nodes as in trav_visit, but the leaf children it enters
-// are not tested in place: a node yields 0-4 of them per lane, so per-child
+// are not tested in place: a node yields 0-6 of them per lane, so per-child
 // tests would run with a handful of the 64 lanes busy.  Instead each candidate
 // (leaf index << 6 | lane) goes into a wave-wide LDS queue, and whenever the
 // queue holds a full round every lane takes one entry, fetches the owner's
@@ -430,8 +421,10 @@ __device__ __forceinline__ void trav_visit(Trav& s, const BvhView& bv, uint2* st
 //
 // Every lane of the wave must call this together (active = false for lanes
 // without a ray).  SCENE_PER_LANE: lanes may trace different scenes (the
-// owner's leaf array and t_eps travel with the candidate).
-#define DT_LQ_CAP 192
+// owner's leaf array and t_eps travel with the candidate).  ANY: a lane stops
+// at its first hit, whichever it is (tri >= 0, t one of its hits'), and
+// triangle skip2 is ignored as well.
+#define DT_LQ_CAP 128
 struct LeafQueue {
   uint32_t req[DT_LQ_CAP];       // (leaf << 6) | owner lane
   unsigned long long best[64];   // per owner: (t bits << 32) | triangle id
@@ -443,16 +436,17 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-template <int SL, bool GLOBAL, bool SCENE_PER_LANE>
+template <int SL, bool GLOBAL, bool SCENE_PER_LANE, bool ANY = false>
 __device__ __forceinline__ Hit closest_hit_wave(const BvhView& bv, bool active, v3 o, v3 d,
                                                 int skip, float t_eps, uint2* stk, int stride,
                                                 uint2* gstk, int gcap, LeafQueue& lq,
-                                                bool* overflow) {
+                                                bool* overflow, int skip2 = -1) {
   const int lane = (int)(threadIdx.x & 63u);
   const uint64_t lt = (1ull << lane) - 1ull;
   Trav s;
   trav_init(s, bv, o, d, skip, t_eps);
   if (!active) s.done = true;
+  if (ANY && bv.nf == 1 && s.h.tri == skip2) s.h.tri = -1;
   lq.best[lane] = ~0ull;
   bool queued = false;  // this lane's best came from the queue
   uint32_t qn = 0;      // queue fill (wave-uniform)
@@ -477,6 +471,8 @@ __device__ __forceinline__ Hit closest_hit_wave(const BvhView& bv, bool active, 
       r.ky = (kp >> 2) & 3;
       r.kz = (kp >> 4) & 3;
       const int sk = __shfl(s.skip, ow);
+      int sk2 = -1;
+      if constexpr (ANY) sk2 = __shfl(skip2, ow);
       const float4* L = bv.leaves;
       float te = t_eps;
       if constexpr (SCENE_PER_LANE) {
@@ -492,7 +488,7 @@ __device__ __forceinline__ Hit closest_hit_wave(const BvhView& bv, bool active, 
         Hit h;
         h.tri = -1;
         h.t = INFINITY;
-        if (f != sk && tri_test(r, xyz(p0), xyz(p1), xyz(p2), f, te, h)) {
+        if (f != sk && (!ANY || f != sk2) && tri_test(r, xyz(p0), xyz(p1), xyz(p2), f, te, h)) {
           const unsigned long long key =
               ((unsigned long long)__float_as_uint(h.t) << 32) | (unsigned long long)(uint32_t)f;
           atomicMin(&lq.best[ow], key);
@@ -507,33 +503,40 @@ __device__ __forceinline__ Hit closest_hit_wave(const BvhView& bv, bool active, 
       s.h.t = __uint_as_float((uint32_t)(kb >> 32));
       s.h.tri = (int)(uint32_t)kb;
       queued = true;
+      if constexpr (ANY) s.done = true;
     }
   };
 
-  uint32_t lf[4] = {0u, 0u, 0u, 0u};
-  uint32_t lm = 0u;
-  auto append = [&](int k) {
-    const bool m = (lm >> k) & 1u;
-    const uint64_t b = __ballot(m);
-    if (m) lq.req[qn + (uint32_t)__popcll(b & lt)] = (lf[k] << 6) | (uint32_t)lane;
-    qn += (uint32_t)__popcll(b);
-  };
-
-  while (__ballot(!s.done) != 0ull) {
-    lm = 0u;
-    if (!s.done) trav_visit<SL, GLOBAL>(s, bv, stk, stride, gstk, gcap, lm, lf);
-    // at most 63 + 2 * 64 entries are held at any time
-    append(0);
-    append(1);
-    rounds(64u);
-    append(2);
-    append(3);
-    rounds(64u);
+  // a depth-first walk visits each node at most once, so no lane needs more
+  // steps than its tree has nodes
+  const uint32_t most = (uint32_t)wide_cap(bv.nf) + 64u;
+  for (uint32_t step = 0; __ballot(!s.done) != 0ull; ++step) {
+    uint32_t lm = 0u, lall = 0u, lbase = 0u;
+    if (!s.done) {
+      if (step > most) {
+        s.overflow = true;
+        s.done = true;
+      } else {
+        trav_visit<SL, GLOBAL>(s, bv, stk, stride, gstk, gcap, lm, lall, lbase);
+      }
+    }
+    // one leaf of every lane that has one left per pass; at most 63 + 64
+    // entries are held at any time
+    for (uint64_t b = __ballot(lm != 0u); b != 0ull; b = __ballot(lm != 0u)) {
+      if (lm != 0u) {
+        const uint32_t bit = lm & (0u - lm);
+        const uint32_t leaf = min(lbase + (uint32_t)__popc(lall & (bit - 1u)), (uint32_t)(bv.nf - 1));
+        lq.req[qn + (uint32_t)__popcll(b & lt)] = (leaf << 6) | (uint32_t)lane;
+        lm &= lm - 1u;
+      }
+      qn += (uint32_t)__popcll(b);
+      if (qn >= 64u) rounds(64u);
+    }
   }
   rounds(1u);
   if (s.overflow) *overflow = true;
   Hit h = s.h;
-  if (queued) {
+  if (!ANY && queued) {
     const float4* L = bv.leaves;
     const uint32_t j = lq.win[lane];
     const float4 p0 = L[3 * j];

@@ -62,7 +62,8 @@ __device__ __forceinline__ v3 load3(const float* p) { return {p[0], p[1], p[2]};
 // ---------------------------------------------------------------- BVH blob
 // Internal node: boxes of both children + child references + parent.
 // A child reference >= 0 is an internal node; (leaf | LEAF_BIT) is a leaf,
-// leaf j being the j-th triangle in Morton order.
+// leaf j being the j-th triangle in Morton order
+// (the binary tree's leaves; the traversal tree numbers them anew).
 #define DT_LEAF_BIT 0x80000000u
 // largest triangle count: the wave traversal packs (leaf index << 6 | lane)
 // into 32 bits
@@ -75,32 +76,44 @@ struct __align__(16) BvhNode {
   int4 d;    // child0 child1 parent unused
 };
 
-// 4-wide node collapsed from the binary tree: a binary internal node at even
-// depth (root = 0) becomes a 4-wide node whose children are its grandchildren
-// (a leaf child stays a leaf), 2 to 4 of them.  A child reference is a 4-wide
-// node index, (leaf | DT_LEAF_BIT), or DT_NO_CHILD for an unused slot.
+// 6-wide traversal node collapsed from the binary tree: starting from a binary
+// internal node's two children, the internal child of largest box area is
+// replaced by its own two children until there are six or only leaves remain.
+// Six 8-bit boxes and everything else a visit needs fit one 64-byte line.
 //
-// The child boxes are stored quantized (64 B per node instead of 128): per
-// axis an origin p and a power of two s = 2^e, and per child and axis 8-bit
-// steps, lo = p + qlo * s, hi = p + qhi * s.  The build chooses p a multiple
-// of s and s large enough that every such value is exactly representable in
-// FP32, rounds qlo down and qhi up, and checks the decoded bounds against the
-// exact child box, so the decoded boxes contain the exact ones and the
-// traversal's decisions stay conservative.
+// The children are sorted by box centre along one axis (`axis`, the one their
+// centres spread most along), so a ray visits them in ascending or, where its
+// direction is negative on that axis, descending order without sorting entry
+// distances.  Child k (bit k of a mask) is internal where imask has its bit
+// and a leaf where lmask has it; internal children have consecutive node
+// indices from child_base and leaves consecutive leaf indices from leaf_base,
+// both in child order, so a child's index is the base plus the number of its
+// kind below it.
+//
+// The child boxes are stored quantized: per axis an origin p and a power of
+// two s = 2^e, and per child and axis 8-bit steps, lo = p + qlo * s,
+// hi = p + qhi * s.  The build chooses p a multiple of s and s large enough
+// that every such value is exactly representable in FP32, rounds qlo down and
+// qhi up, and checks the decoded bounds against the exact child box, so the
+// decoded boxes contain the exact ones and the traversal's decisions stay
+// conservative.
 #define DT_NO_CHILD 0xFFFFFFFFu
+#define DT_WIDE 6
+#define DT_WIDE_INDEX 0x03FFFFFFu  // the 26 index bits of child_base
 
-struct __align__(16) Bvh4Node {
-  float4 org;   // p.x, p.y, p.z; w: bits e_x | e_y << 8 | e_z << 16 (int8 each) | count << 24
-  uint4 qlo;    // x, y, z: the four children's 8-bit lower steps on that axis (child k in byte k)
-  uint4 qhi;    // x, y, z: upper steps; w unused
-  uint4 child;  // child references
+struct __align__(64) WideNode {
+  float4 org;  // p.x, p.y, p.z; w: bits e_x | e_y << 8 | e_z << 16 (int8 each) | imask << 24 | axis << 30
+  uint4 a;     // child_base | lmask << 26, leaf_base, x lower steps of children 0-3, x upper steps
+  uint4 b;     // y lower, y upper, z lower, z upper steps of children 0-3
+  uint4 c;     // x, y, z: steps of children 4, 5 (lower in bytes 0, 1, upper in bytes 2, 3); w unused
 };
 
-// Upper bound on the number of 4-wide nodes: with E even-depth and O odd-depth
-// internal nodes, every even one but the root has an odd parent with at most
-// two internal children, so E - 1 <= 2 O and E <= (2 (nf - 1) + 1) / 3.
-__host__ __device__ inline int32_t bvh4_cap(int32_t nf) {
-  return nf > 1 ? (int32_t)((2 * (int64_t)(nf - 1) + 1) / 3) : 1;
+// Upper bound on the number of 6-wide nodes: a node has six children or only
+// leaves (at least two).  With A nodes of six children and B smaller ones,
+// counting children gives 5 A + B <= nf - 1 and, as each of the B hangs off
+// one of the A (or is the root), B <= 5 A + 1, so A + B <= (3 nf - 1) / 5.
+__host__ __device__ inline int32_t wide_cap(int32_t nf) {
+  return (int32_t)((3 * (int64_t)nf) / 5) + 1;
 }
 
 struct BvhHeader {
@@ -112,7 +125,7 @@ struct BvhHeader {
 
 // Byte offsets inside the caller's blob; a pure function of (nv, nf).
 struct BvhLayout {
-  size_t header, nodes, nodes4, leaves, vnormals, fnormals, csr_off, csr_idx, leaf_parent, total;
+  size_t header, nodes, wide, leaves, vnormals, fnormals, csr_off, csr_idx, leaf_parent, total;
 };
 
 __host__ __device__ inline size_t dt_align(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
@@ -124,8 +137,8 @@ inline BvhLayout bvh_layout(int32_t nv, int32_t nf) {
   o = dt_align(o + sizeof(BvhHeader));
   L.nodes = o;
   o = dt_align(o + sizeof(BvhNode) * (size_t)(nf > 1 ? nf - 1 : 1));
-  L.nodes4 = o;
-  o = dt_align(o + sizeof(Bvh4Node) * (size_t)bvh4_cap(nf));
+  L.wide = o;
+  o = dt_align(o + sizeof(WideNode) * (size_t)wide_cap(nf));
   L.leaves = o;
   o = dt_align(o + sizeof(float4) * 3 * (size_t)nf);
   L.vnormals = o;
@@ -146,8 +159,8 @@ inline BvhLayout bvh_layout(int32_t nv, int32_t nf) {
 struct BvhView {
   const BvhHeader* hdr;
   const BvhNode* nodes;
-  const Bvh4Node* nodes4;  // traversal tree
-  const float4* leaves;    // 3 per leaf: v0 (w = tri id bits), v1, v2
+  const WideNode* wide;    // traversal tree
+  const float4* leaves;    // 3 per leaf: v0 (w = tri id bits), v1, v2, in the traversal tree's leaf order
   const float4* vn;      // vertex normals
   const float4* fn;      // unit face normals (w = 1 if area > 0)
   const int32_t* csr_off;
@@ -161,7 +174,7 @@ inline BvhView bvh_view(const void* blob, int32_t nv, int32_t nf) {
   BvhView v;
   v.hdr = (const BvhHeader*)(b + L.header);
   v.nodes = (const BvhNode*)(b + L.nodes);
-  v.nodes4 = (const Bvh4Node*)(b + L.nodes4);
+  v.wide = (const WideNode*)(b + L.wide);
   v.leaves = (const float4*)(b + L.leaves);
   v.vn = (const float4*)(b + L.vnormals);
   v.fn = (const float4*)(b + L.fnormals);
