@@ -59,6 +59,33 @@ __device__ __forceinline__ bool claim_batch(WorkPart* wp, uint32_t nb, uint32_t 
   }
 }
 
+// Rays a wave takes at a time.  A long queue is traced 64 rays to a wave.  A
+// queue too short to give every SIMD of the chip a wave that way is bound by
+// the longest chain of node visits in a wave, and by the 64 separate lines a
+// wave's node fetch asks for, so its batches shrink, to no less than 8 rays,
+// until there are DT_WAVES_WANTED of them (one per SIMD): measured per launch,
+// 5,000 rays on 102,400 faces 81 -> 75 us, 4,096 rays on 1,280 faces 32 -> 25 us.
+constexpr uint32_t DT_WAVES_WANTED = 1024;
+constexpr uint32_t DT_MIN_BATCH = 8;
+__device__ __forceinline__ uint32_t batch_rays(uint32_t n) {
+  uint32_t r = 64;
+  while (r > DT_MIN_BATCH && n < r * DT_WAVES_WANTED) r >>= 1;
+  return r;
+}
+
+// The calling wave's next batch: where the grid has a workgroup (of one wave)
+// for every batch, workgroup b takes batch b and nothing else, without the
+// claims' round trips (an empty queue part costs one too); else claim_batch.
+// first: true on the wave's first call.
+__device__ __forceinline__ bool next_batch(WorkPart* wp, uint32_t nb, uint32_t x0, uint32_t& p, uint32_t& batch,
+                                           bool& first) {
+  if (nb > gridDim.x) return claim_batch(wp, nb, x0, p, batch);
+  batch = blockIdx.x;
+  const bool mine = first && batch < nb;
+  first = false;
+  return mine;
+}
+
 // Device-side counters of a trace (also the tape header).
 struct Counters {
   uint32_t count[DT_MAX_DEPTH + 2];  // rays in generation g
@@ -112,6 +139,62 @@ dt_status make_camera(const dt_camera& cam, int index, CamDev& cd);
 constexpr int DT_CHUNK = 2048;
 dt_status chunk_scan(Counters* ctr, int g, unsigned long long* part, unsigned long long* other,
                      int64_t other_n, int64_t cap_next, hipStream_t s);
+
+// Positions of the children of the rays [blk * EMIT_T, (blk + 1) * EMIT_T) of a
+// generation in the next queue, one ray per thread of a block: reflected
+// children fill [0, nrefl) in ray order, refracted ones follow.  part holds the
+// exclusive scan of the children per chunk of DT_CHUNK rays; what the chunk's
+// earlier rays emit is counted from their codes (at most 7 KB, read by the
+// whole block at once), so every block does one step of work: with a block
+// walking its chunk in eight dependent steps a short queue's few chunks took
+// 18 us (4,096 rays) where they now take 6.  h_r, h_t: this thread's ray emits them.
+constexpr int EMIT_T = 256;
+
+struct EmitLds {
+  uint32_t r[EMIT_T / 64], t[EMIT_T / 64];    // this step's children per wave
+  uint32_t er[EMIT_T / 64], et[EMIT_T / 64];  // the chunk's earlier ones, as counted by each wave
+};
+
+__device__ __forceinline__ uint2 child_positions(const uint32_t* code, int64_t blk, const unsigned long long* part,
+                                                 uint32_t nrefl, bool h_r, bool h_t, EmitLds& lds) {
+  constexpr int PER = DT_CHUNK / EMIT_T;
+  const int lane = (int)(threadIdx.x & 63u), wv = (int)(threadIdx.x >> 6);
+  const int64_t chunk = blk / PER;
+  const int before = (int)(blk % PER);
+  const uint32_t* c0 = code + chunk * DT_CHUNK + threadIdx.x;
+  uint32_t er = 0, et = 0;
+#pragma unroll
+  for (int k = 0; k < PER - 1; ++k) {
+    const uint32_t c = k < before ? c0[k * EMIT_T] : 0u;
+    er += (uint32_t)__popcll(__ballot((c & C_HAS_R) != 0u));
+    et += (uint32_t)__popcll(__ballot((c & C_HAS_T) != 0u));
+  }
+  const uint64_t br = __ballot(h_r), bt = __ballot(h_t);
+  if (lane == 0) {
+    lds.r[wv] = (uint32_t)__popcll(br);
+    lds.t[wv] = (uint32_t)__popcll(bt);
+    lds.er[wv] = er;
+    lds.et[wv] = et;
+  }
+  __syncthreads();
+  const unsigned long long base = part[chunk];
+  const uint64_t lt = (1ull << lane) - 1ull;
+  uint32_t ir = (uint32_t)base + (uint32_t)__popcll(br & lt);
+  uint32_t it = nrefl + (uint32_t)(base >> 32) + (uint32_t)__popcll(bt & lt);
+#pragma unroll
+  for (int k = 0; k < EMIT_T / 64; ++k) {
+    ir += lds.er[k] + (k < wv ? lds.r[k] : 0u);
+    it += lds.et[k] + (k < wv ? lds.t[k] : 0u);
+  }
+  __syncthreads();  // before the next step's counts
+  return make_uint2(ir, it);
+}
+
+// blocks of EMIT_T threads that walk a queue of at most cap rays
+inline unsigned emit_grid(int64_t cap) {
+  const int64_t b = (cap + EMIT_T - 1) / EMIT_T;
+  return (unsigned)(b < 1 ? 1 : (b < 16384 ? b : 16384));
+}
 
 // environment MLP launchers (env_mlp.hip)
 bool mlp_supported(const EnvDev& e);

@@ -154,7 +154,7 @@ __device__ __forceinline__ bool silhouette_edge(const float* V, const int32_t* F
 // (edge, camera) pairs and carry the only costly work, so the wave first
 // collects them in LDS and then deals their quadrature points to its lanes
 // (a thread per (edge, camera) that walked the tree for its own points left
-// one lane in fifty busy: 1,172 against 86 us for 8 views of 512 x 512 and
+// one lane in fifty busy: 1,172 against 204 us for 8 views of 512 x 512 and
 // 102,400 faces).
 // counts: [0] outline points in an image where the loss gradient is nonzero,
 // [1] of those, points on the outline (visible), [2] stack overflows

@@ -18,7 +18,6 @@
 namespace {
 
 constexpr int TBS = 64;
-constexpr int EBS = 256;
 
 // ray flag word
 constexpr uint32_t SF_INSIDE = 1u;
@@ -189,13 +188,14 @@ __global__ void __launch_bounds__(TBS, 7) k_serve_trace(const ServeTables* T, Ge
   Counters* ctr = &st->ctr;
   const uint32_t n = ctr->count[0];
   const int lane = threadIdx.x & 63;
-  const uint32_t nb = (n + 63u) / 64u;
+  const uint32_t rays = batch_rays(n), nb = (n + rays - 1u) / rays;
   const uint32_t x0 = blockIdx.x % (unsigned)DT_WORK_PARTS;
   uint32_t p = x0, batch = 0;
-  while (claim_batch(st->wp, nb, x0, p, batch)) {
-    const uint32_t base = batch * 64u;
+  bool first = true;
+  while (next_batch(st->wp, nb, x0, p, batch, first)) {
+    const uint32_t base = batch * rays;
     uint32_t i = base + lane;
-    const bool active = i < n;
+    const bool active = i < n && (uint32_t)lane < rays;
     bool has_r = false, has_t = false;
     float4 o4 = make_float4(0.f, 0.f, 0.f, __int_as_float(-1)), d4 = make_float4(0.f, 0.f, 1.f, 0.f);
     if (active) {
@@ -307,41 +307,20 @@ __global__ void k_serve_zero_nmiss(ServeState* st) {
   if (threadIdx.x == 0 && blockIdx.x == 0) st->ctr.nmiss[0] = 0;
 }
 
-__global__ void __launch_bounds__(EBS) k_serve_emit(const ServeTables* T, Gen q, Gen nx,
-                                                    ServeState* st, const unsigned long long* part,
-                                                    int64_t cap, ServeOut out) {
-  __shared__ uint32_t wr[EBS / 64], wt[EBS / 64];
+__global__ void __launch_bounds__(EMIT_T) k_serve_emit(const ServeTables* T, Gen q, Gen nx,
+                                                       ServeState* st, const unsigned long long* part,
+                                                       int64_t cap, ServeOut out) {
+  __shared__ EmitLds lds;
   Counters* ctr = &st->ctr;
   const uint32_t n = ctr->count[0];
-  const int64_t base = (int64_t)blockIdx.x * DT_CHUNK;
-  if (base >= n) return;
   const uint32_t nr_tot = ctr->nrefl[0];
-  unsigned long long c = part[blockIdx.x];
-  uint32_t carry_r = (uint32_t)(c & 0xffffffffull), carry_t = (uint32_t)(c >> 32);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const uint64_t lt = (1ull << lane) - 1ull;
-  for (int s = 0; s < DT_CHUNK / EBS; ++s) {
-    int64_t i = base + (int64_t)s * EBS + threadIdx.x;
+  for (int64_t blk = blockIdx.x; blk * EMIT_T < n; blk += gridDim.x) {
+    int64_t i = blk * EMIT_T + threadIdx.x;
     bool active = i < n;
     uint32_t code = active ? q.code[i] : 0u;
     bool hr = (code & C_HAS_R) != 0u, ht = (code & C_HAS_T) != 0u;
-    uint64_t br = __ballot(hr), bt = __ballot(ht);
-    if (lane == 0) {
-      wr[wv] = (uint32_t)__popcll(br);
-      wt[wv] = (uint32_t)__popcll(bt);
-    }
-    __syncthreads();
-    uint32_t or_ = 0, ot = 0, tr = 0, tt = 0;
-    for (int k = 0; k < EBS / 64; ++k) {
-      if (k < wv) {
-        or_ += wr[k];
-        ot += wt[k];
-      }
-      tr += wr[k];
-      tt += wt[k];
-    }
-    uint32_t ir = carry_r + or_ + (uint32_t)__popcll(br & lt);
-    uint32_t it = nr_tot + carry_t + ot + (uint32_t)__popcll(bt & lt);
+    const uint2 at = child_positions(q.code, blk, part, nr_tot, hr, ht, lds);
+    const uint32_t ir = at.x, it = at.y;
     if (active && (hr || ht)) {
       float4 o4 = q.o[i], d4 = q.d[i], w4 = q.w[i], h4 = q.hit[i];
       v3 o = xyz(o4), d = xyz(d4), W = xyz(w4);
@@ -378,9 +357,6 @@ __global__ void __launch_bounds__(EBS) k_serve_emit(const ServeTables* T, Gen q,
         }
       }
     }
-    carry_r += tr;
-    carry_t += tt;
-    __syncthreads();
   }
 }
 
@@ -544,7 +520,7 @@ extern "C" dt_status dt_serve_step(const dt_serve_scene* scenes, int32_t n_scene
   if (added) hipLaunchKernelGGL(k_serve_admit_count, dim3(1), dim3(64), 0, s, st, added, L.cap);
   DT_CHECK_LAUNCH();
   // one interaction for every live ray
-  hipLaunchKernelGGL(k_serve_trace, dim3(grid_for(L.cap, TBS, SERVE_TRACE_BLOCKS)), dim3(TBS), 0, s,
+  hipLaunchKernelGGL(k_serve_trace, dim3(grid_for(L.cap, DT_MIN_BATCH, SERVE_TRACE_BLOCKS)), dim3(TBS), 0, s,
                      Td, qc, st, part[cur], out, (uint2*)(W + L.ovf));
   // MLP environments: list each one's misses, evaluate them on the matrix cores
   for (int e = 0; e < n_envs; ++e) {
@@ -557,7 +533,7 @@ extern "C" dt_status dt_serve_step(const dt_serve_scene* scenes, int32_t n_scene
     if (dt_status er = mlp_trace_forward(T.env[e], qc, list, &st->ctr, 0, L.cap, pixels, s)) return er;
   }
   if (dt_status e = chunk_scan(&st->ctr, 0, part[cur], part[nxt], L.maxchunks + 1, L.cap, s)) return e;
-  hipLaunchKernelGGL(k_serve_emit, dim3((unsigned)L.maxchunks), dim3(EBS), 0, s, Td, qc, qn, st,
+  hipLaunchKernelGGL(k_serve_emit, dim3(emit_grid(L.cap)), dim3(EMIT_T), 0, s, Td, qc, qn, st,
                      part[cur], L.cap, out);
   // (the scan zeroed part[nxt] for the next step; the next step's scan zeroes part[cur])
   hipLaunchKernelGGL(k_serve_advance, dim3(1), dim3(64), 0, s, st);

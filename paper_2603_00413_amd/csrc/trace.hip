@@ -23,7 +23,6 @@ namespace {
 
 constexpr int TB = 64;                // threads per block of the traversal kernel (one wave)
 constexpr int CHUNK = DT_CHUNK;       // rays per compaction chunk
-constexpr int EB = 256;               // threads per block of the emit kernel
 constexpr int AB = 256;               // threads per block of the adjoint kernel
 constexpr int ADJ_MAX_BLOCKS = 4096;  // grid cap of the adjoint kernel
 constexpr int TRACE_MAX_BLOCKS = 256 * 4 * 7;  // grid cap of the traversal kernel: 7 resident waves per SIMD
@@ -301,14 +300,15 @@ __global__ void __launch_bounds__(TB, FIELD ? 4 : 7) k_trace(SceneDev sc, Gen q,
   uint2* gstk = ovf + (size_t)(blockIdx.x * TB + threadIdx.x) * (DT_STACK - DT_STACK_LDS);
   const uint32_t n = ctr->count[g];
   const int lane = threadIdx.x & 63;
-  const uint32_t nb = (n + 63u) / 64u;
+  const uint32_t rays = batch_rays(n), nb = (n + rays - 1u) / rays;
   const uint32_t x0 = blockIdx.x % (unsigned)DT_WORK_PARTS;
   uint32_t p = x0, batch = 0;
+  bool first = true;
   wp += (size_t)g * DT_WORK_PARTS;
-  while (claim_batch(wp, nb, x0, p, batch)) {
-    const uint32_t base = batch * 64u;
+  while (next_batch(wp, nb, x0, p, batch, first)) {
+    const uint32_t base = batch * rays;
     uint32_t i = base + lane;
-    bool active = i < n;
+    bool active = i < n && (uint32_t)lane < rays;
     bool has_r = false, has_t = false, hit = false;
     float4 o4 = make_float4(0.f, 0.f, 0.f, __int_as_float(-1)), d4 = make_float4(0.f, 0.f, 1.f, 0.f);
     if (active) {
@@ -436,44 +436,25 @@ __global__ void k_scan(Counters* ctr, int g, unsigned long long* part, unsigned 
 }
 
 // ------------------------------------------------------------------ k_emit (a5 children)
-// Block b re-walks chunk b in order and writes each ray's children at its
-// scanned position: reflected children fill [0, n_r) of the next queue,
-// refracted children [n_r, n_r + n_t).  write_rays = 0 computes indices only.
+// Each step of a block writes EMIT_T consecutive rays' children at their
+// scanned positions (child_positions): reflected children fill [0, n_r) of the
+// next queue, refracted children [n_r, n_r + n_t).  write_rays = 0 computes
+// indices only.  Long queues run at the rate of their 84 B a parent and 48 B a
+// child (54 us for 2 M parents, 5 TB/s).
 template <bool GRID, bool FIELD>
-__global__ void __launch_bounds__(EB) k_emit(SceneDev sc, Gen q, Gen nx, int g, Counters* ctr,
-                                             const unsigned long long* part, int64_t cap_next,
-                                             int write_rays, int32_t* flags, const float4* att) {
-  __shared__ uint32_t wr[EB / 64], wt[EB / 64];
+__global__ void __launch_bounds__(EMIT_T) k_emit(SceneDev sc, Gen q, Gen nx, int g, Counters* ctr,
+                                                 const unsigned long long* part, int64_t cap_next,
+                                                 int write_rays, int32_t* flags, const float4* att) {
+  __shared__ EmitLds lds;
   const uint32_t n = ctr->count[g];
-  const int64_t base = (int64_t)blockIdx.x * CHUNK;
-  if (base >= n) return;
   const uint32_t nr_tot = ctr->nrefl[g];
-  unsigned long long c = part[blockIdx.x];
-  uint32_t carry_r = (uint32_t)(c & 0xffffffffull), carry_t = (uint32_t)(c >> 32);
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const uint64_t lt = (1ull << lane) - 1ull;
-  for (int s = 0; s < CHUNK / EB; ++s) {
-    int64_t i = base + (int64_t)s * EB + threadIdx.x;
+  for (int64_t blk = blockIdx.x; blk * EMIT_T < n; blk += gridDim.x) {
+    int64_t i = blk * EMIT_T + threadIdx.x;
     bool active = i < n;
     uint32_t code = active ? q.code[i] : 0u;
     bool hr = (code & C_HAS_R) != 0u, ht = (code & C_HAS_T) != 0u;
-    uint64_t br = __ballot(hr), bt = __ballot(ht);
-    if (lane == 0) {
-      wr[wv] = (uint32_t)__popcll(br);
-      wt[wv] = (uint32_t)__popcll(bt);
-    }
-    __syncthreads();
-    uint32_t or_ = 0, ot = 0, tr = 0, tt = 0;
-    for (int k = 0; k < EB / 64; ++k) {
-      if (k < wv) {
-        or_ += wr[k];
-        ot += wt[k];
-      }
-      tr += wr[k];
-      tt += wt[k];
-    }
-    uint32_t ir = carry_r + or_ + (uint32_t)__popcll(br & lt);
-    uint32_t it = nr_tot + carry_t + ot + (uint32_t)__popcll(bt & lt);
+    const uint2 at = child_positions(q.code, blk, part, nr_tot, hr, ht, lds);
+    const uint32_t ir = at.x, it = at.y;
     if (active) {
       int cr = -1, ctd = -1;
       if (hr || ht) {
@@ -528,9 +509,6 @@ __global__ void __launch_bounds__(EB) k_emit(SceneDev sc, Gen q, Gen nx, int g, 
       }
       if (q.child) q.child[i] = make_int2(cr, ctd);
     }
-    carry_r += tr;
-    carry_t += tt;
-    __syncthreads();
   }
 }
 
@@ -1729,7 +1707,7 @@ unsigned list_grid(int64_t cap) {
 }
 
 unsigned trace_grid(int64_t cap) {
-  int64_t waves = (cap + 63) / 64;
+  int64_t waves = (cap + DT_MIN_BATCH - 1) / DT_MIN_BATCH;  // a wave per smallest batch (batch_rays)
   int64_t lim = TRACE_MAX_BLOCKS;  // resident waves the LDS stack allows on 256 CUs
   return (unsigned)(waves < lim ? (waves < 1 ? 1 : waves) : lim);
 }
@@ -1794,9 +1772,8 @@ dt_status run_generation(const SceneDev& sc, const Plan& P, int g, Gen cur, Gen 
     int64_t other_n = (P.cap[g + 1] + CHUNK - 1) / CHUNK + 1;
     hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, ctr, g, part_g, part_other, other_n,
                        P.cap[g + 1]);
-    int64_t nch = (P.cap[g] + CHUNK - 1) / CHUNK;
 #define DT_EMIT(G, FL)                                                                                 \
-  hipLaunchKernelGGL((k_emit<G, FL>), dim3((unsigned)nch), dim3(EB), 0, s, sc, cur, nxt, g, ctr, part_g, \
+  hipLaunchKernelGGL((k_emit<G, FL>), dim3(emit_grid(P.cap[g])), dim3(EMIT_T), 0, s, sc, cur, nxt, g, ctr, part_g, \
                      P.cap[g + 1], write_next, accumulate ? flags : nullptr, att)
     if (sc.fd.grid) {
       if (sc.ab.mu) DT_EMIT(true, true); else DT_EMIT(false, true);
