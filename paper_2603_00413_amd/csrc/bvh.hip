@@ -12,7 +12,8 @@
 namespace {
 
 constexpr int SCAN_NB = 256;  // blocks (= partial sums) of the chunked device scan
-constexpr int TREELET_PASSES = 4;  // treelet restructuring passes after the box fit
+constexpr int TILE_PASSES = 8;  // treelet restructuring passes inside the tiles
+constexpr int TOP_PASSES = 2;   // and over the nodes that span tiles
 constexpr int SCAN_T = 256;
 
 // ------------------------------------------------------------------ block scans
@@ -47,16 +48,19 @@ __global__ void k_scan_reduce(const T* in, int32_t n, int32_t chunk, T* part) {
   if (threadIdx.x == blockDim.x - 1) part[blockIdx.x] = tot;
 }
 
-// exclusive scan of part[0..nb) in place; part[nb] = total
+// exclusive scan of part[0..nb) in place; part[nb] = total, also to *total
 template <class T>
-__global__ void k_scan_partials(T* part, int nb) {
+__global__ void k_scan_partials(T* part, int nb, T* total) {
   __shared__ T sh[SCAN_NB];
   int t = threadIdx.x;
   T v = t < nb ? part[t] : 0;
   T inc = block_incl_scan(v, sh);
   __syncthreads();
   if (t < nb) part[t] = inc - v;
-  if (t == (int)blockDim.x - 1) part[nb] = inc;
+  if (t == (int)blockDim.x - 1) {
+    part[nb] = inc;
+    if (total) *total = inc;
+  }
 }
 
 template <class T>
@@ -76,8 +80,53 @@ __global__ void k_scan_apply(const T* in, T* out, int32_t n, int32_t chunk, cons
   }
 }
 
-__global__ void k_copy_total(const int32_t* part, int nb, int32_t* dst) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *dst = part[nb];
+// the whole scan in one block, SCAN_ONE elements a step: a launch costs about as
+// much as two steps (2.4 us each), so up to SCAN_ONE_MAX elements it beats the
+// three kernels above (10 us)
+constexpr int SCAN_ONE_T = 1024;
+constexpr int SCAN_ONE = 4 * SCAN_ONE_T;
+constexpr int SCAN_ONE_MAX = 2 * SCAN_ONE;
+template <class T>
+__global__ void __launch_bounds__(SCAN_ONE_T) k_scan_one(const T* in, T* out, int32_t n, T* part, T* total) {
+  __shared__ T wsum[SCAN_ONE_T / 64];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  T carry = 0;
+  for (int base = 0; base < n; base += SCAN_ONE) {
+    const int i = base + 4 * t;
+    T v[4], s = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      v[k] = i + k < n ? in[i + k] : (T)0;
+      s += v[k];
+    }
+    T inc = s;
+#pragma unroll
+    for (int st = 1; st < 64; st <<= 1) {
+      const T up = __shfl_up(inc, st);
+      if (lane >= st) inc += up;
+    }
+    if (lane == 63) wsum[wv] = inc;
+    __syncthreads();
+    T before = carry, all = 0;
+#pragma unroll
+    for (int k = 0; k < SCAN_ONE_T / 64; ++k) {
+      const T w = wsum[k];
+      before += k < wv ? w : (T)0;
+      all += w;
+    }
+    T run = before + inc - s;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (i + k < n) out[i + k] = run;
+      run += v[k];
+    }
+    carry += all;
+    __syncthreads();
+  }
+  if (t == 0) {
+    part[SCAN_NB] = carry;
+    if (total) *total = carry;
+  }
 }
 
 // ------------------------------------------------------------------ normals
@@ -86,14 +135,34 @@ __device__ __forceinline__ bool face_ok(const int32_t* F, int f, int32_t nv) {
   return a >= 0 && a < nv && b >= 0 && b < nv && c >= 0 && c < nv;
 }
 
-__global__ void k_face_normals(const float* V, const int32_t* F, int32_t nf, int32_t nv, float4* fn) {
+// header, and the vertices' face counts cleared
+__global__ void k_build_init(BvhHeader* hdr, int32_t nv, int32_t nf, int32_t* cnt) {
+  const int v = blockIdx.x * blockDim.x + threadIdx.x;
+  if (v < nv) cnt[v] = 0;
+  if (v == 0) {
+    hdr->nv = nv;
+    hdr->nf = nf;
+    hdr->depth = nf == 1 ? 1 : 0;  // larger trees: k_wide_roots
+    hdr->pad0 = 0;
+  }
+}
+
+// Unit face normals, and the vertices' incident faces counted: corner k of
+// face f is its vertex's rank[3 f + k]-th, in the order the atomics arrive
+// (k_vnormals sorts the lists)
+__global__ void k_faces(const float* V, const int32_t* F, int32_t nf, int32_t nv, float4* fn, int32_t* cnt,
+                        int32_t* rank) {
   int f = blockIdx.x * blockDim.x + threadIdx.x;
   if (f >= nf) return;
   if (!face_ok(F, f, nv)) {
     fn[f] = make_float4(0.f, 0.f, 0.f, 0.f);
     return;
   }
-  v3 a = load3(V + 3 * F[3 * f]), b = load3(V + 3 * F[3 * f + 1]), c = load3(V + 3 * F[3 * f + 2]);
+  const int i0 = F[3 * f], i1 = F[3 * f + 1], i2 = F[3 * f + 2];
+  rank[3 * (size_t)f] = atomicAdd(&cnt[i0], 1);
+  rank[3 * (size_t)f + 1] = atomicAdd(&cnt[i1], 1);
+  rank[3 * (size_t)f + 2] = atomicAdd(&cnt[i2], 1);
+  v3 a = load3(V + 3 * i0), b = load3(V + 3 * i1), c = load3(V + 3 * i2);
   v3 n = cross(b - a, c - a);
   float l2 = dot(n, n);
   if (l2 > 0.0f) {
@@ -104,28 +173,21 @@ __global__ void k_face_normals(const float* V, const int32_t* F, int32_t nf, int
   }
 }
 
-__global__ void k_vcount(const int32_t* F, int32_t nf, int32_t nv, int32_t* cnt) {
-  int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f >= nf || !face_ok(F, f, nv)) return;
-  for (int k = 0; k < 3; ++k) atomicAdd(&cnt[F[3 * f + k]], 1);
-}
-
 __global__ void k_vfill(const int32_t* F, int32_t nf, int32_t nv, const int32_t* off,
-                        int32_t* cursor, int32_t* idx) {
+                        const int32_t* rank, int32_t* idx) {
   int f = blockIdx.x * blockDim.x + threadIdx.x;
   if (f >= nf || !face_ok(F, f, nv)) return;
-  for (int k = 0; k < 3; ++k) {
-    int v = F[3 * f + k];
-    int p = atomicAdd(&cursor[v], 1);
-    idx[off[v] + p] = f;
-  }
+  for (int k = 0; k < 3; ++k) idx[off[F[3 * f + k]] + rank[3 * (size_t)f + k]] = f;
 }
 
-// each vertex's face list in ascending face order (fixed summation order)
-__global__ void k_vsort(const int32_t* off, int32_t nv, int32_t* idx) {
+// Each vertex's face list in ascending face order (fixed summation order), and
+// Eq. 13: one third of the sum of the unit normals of the incident faces, in that
+// order (not renormalised: the shading normal normalises the barycentric blend
+// of Eq. 12 instead)
+__global__ void k_vnormals(const int32_t* off, int32_t* idx, const float4* fn, int32_t nv, float4* vn) {
   int v = blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= nv) return;
-  int lo = off[v], hi = off[v + 1];
+  const int lo = off[v], hi = off[v + 1];
   for (int i = lo + 1; i < hi; ++i) {
     int x = idx[i];
     int j = i - 1;
@@ -135,17 +197,8 @@ __global__ void k_vsort(const int32_t* off, int32_t nv, int32_t* idx) {
     }
     idx[j + 1] = x;
   }
-}
-
-// Eq. 13: one third of the sum of the unit normals of the incident faces, in
-// ascending face order (not renormalised: the shading normal normalises the
-// barycentric blend of Eq. 12 instead)
-__global__ void k_vnormals(const int32_t* off, const int32_t* idx, const float4* fn, int32_t nv,
-                           float4* vn) {
-  int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= nv) return;
   v3 s = mk3(0.f, 0.f, 0.f);
-  for (int i = off[v]; i < off[v + 1]; ++i) s += xyz(fn[idx[i]]);
+  for (int i = lo; i < hi; ++i) s += xyz(fn[idx[i]]);
   v3 n = s * (1.0f / 3.0f);
   vn[v] = make_float4(n.x, n.y, n.z, 0.0f);
 }
@@ -208,57 +261,68 @@ __device__ __forceinline__ uint32_t quant21(float c, float lo, float ext) {
 }
 
 // keys: 63-bit Morton codes of the centroids (21 bits per axis) shifted right
-// by `drop` bits (31 keeps the top 32, about 11 bits per axis)
-// the scene bounds of the centroids from the per-block partials (one block of
-// NBB threads), into the header
-__global__ void __launch_bounds__(NBB) k_bounds_final(const float* part, BvhHeader* hdr) {
-  __shared__ float sh[6][NBB];
+// by `drop` bits (31 keeps the top 32, about 11 bits per axis).  Every block
+// reduces k_bounds' partials to the scene bounds for itself; block 0 also
+// writes them to the header.
+template <class K>
+__global__ void __launch_bounds__(NBB) k_morton(const float* V, const int32_t* F, int32_t nf, int32_t nv, int drop,
+                                                const float* part, BvhHeader* hdr, K* keys, int32_t* vals) {
+  __shared__ float sh[NBB / 64][6];
   const int t = threadIdx.x;
-  for (int k = 0; k < 6; ++k) sh[k][t] = part[t * 6 + k];
-  __syncthreads();
-  for (int st = NBB / 2; st > 0; st >>= 1) {
-    if (t < st)
-      for (int k = 0; k < 3; ++k) {
-        sh[k][t] = fminf(sh[k][t], sh[k][t + st]);
-        sh[3 + k][t] = fmaxf(sh[3 + k][t], sh[3 + k][t + st]);
-      }
-    __syncthreads();
+  float bb[6];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    float x = part[t * 6 + k];
+#pragma unroll
+    for (int st = 32; st > 0; st >>= 1) {
+      const float y = __shfl_xor(x, st);
+      x = k < 3 ? fminf(x, y) : fmaxf(x, y);
+    }
+    if ((t & 63) == 0) sh[t >> 6][k] = x;
   }
-  if (t < 3) hdr->lo[t] = sh[t][0];
-  if (t >= 3 && t < 6) hdr->hi[t - 3] = sh[t][0];
-}
-
-__global__ void k_morton(const float* V, const int32_t* F, int32_t nf, int32_t nv, int drop,
-                         const BvhHeader* hdr, uint64_t* keys, int32_t* vals) {
-  const float bb[6] = {hdr->lo[0], hdr->lo[1], hdr->lo[2], hdr->hi[0], hdr->hi[1], hdr->hi[2]};
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    bb[k] = sh[0][k];
+#pragma unroll
+    for (int w = 1; w < NBB / 64; ++w) bb[k] = k < 3 ? fminf(bb[k], sh[w][k]) : fmaxf(bb[k], sh[w][k]);
+  }
+  if (blockIdx.x == 0 && t == 0)
+    for (int k = 0; k < 3; ++k) {
+      hdr->lo[k] = bb[k];
+      hdr->hi[k] = bb[3 + k];
+    }
+  const int f = blockIdx.x * NBB + t;
   if (f >= nf) return;
   v3 c = centroid(V, F, f, nv);
   uint32_t qx = quant21(c.x, bb[0], bb[3] - bb[0]);
   uint32_t qy = quant21(c.y, bb[1], bb[4] - bb[1]);
   uint32_t qz = quant21(c.z, bb[2], bb[5] - bb[2]);
-  keys[f] = ((spread21(qx) << 2) | (spread21(qy) << 1) | spread21(qz)) >> drop;
+  keys[f] = (K)(((spread21(qx) << 2) | (spread21(qy) << 1) | spread21(qz)) >> drop);
   vals[f] = f;
 }
 
 // ------------------------------------------------------------------ stable LSD radix sort
 constexpr int RS_T = 256;
-constexpr int RS_ITEMS = 8;
-constexpr int RS_TILE = RS_T * RS_ITEMS;
+constexpr int RS_ITEMS = 8;  // keys per thread of the tile; 4 for short sorts (sort_and_link)
+// SELF (short sorts): the histogram is [tile][digit] and each scatter block adds
+// up the few tiles' columns itself; otherwise it is [digit][tile], scanned in
+// place between the two kernels.
 constexpr int RS_WAVES = RS_T / 64;
 
-__global__ void k_rs_hist(const uint64_t* keys, int32_t n, int shift, int32_t* hist, int ntiles) {
+template <class K, int ITEMS, bool SELF>
+__global__ void k_rs_hist(const K* keys, int32_t n, int shift, int32_t* hist, int ntiles) {
   __shared__ uint32_t h[256];
   for (int i = threadIdx.x; i < 256; i += blockDim.x) h[i] = 0;
   __syncthreads();
-  int64_t base = (int64_t)blockIdx.x * RS_TILE;
-  for (int j = 0; j < RS_ITEMS; ++j) {
+  int64_t base = (int64_t)blockIdx.x * (RS_T * ITEMS);
+  for (int j = 0; j < ITEMS; ++j) {
     int64_t i = base + (int64_t)j * RS_T + threadIdx.x;
     if (i < n) atomicAdd(&h[(uint32_t)(keys[i] >> shift) & 255u], 1u);
   }
   __syncthreads();
   for (int dg = threadIdx.x; dg < 256; dg += blockDim.x)
-    hist[(size_t)dg * ntiles + blockIdx.x] = (int32_t)h[dg];
+    hist[SELF ? (size_t)blockIdx.x * 256 + dg : (size_t)dg * ntiles + blockIdx.x] = (int32_t)h[dg];
 }
 
 // lanes of the wave holding the same 8-bit digit (restricted to valid lanes)
@@ -272,16 +336,17 @@ __device__ __forceinline__ uint64_t digit_peers(uint32_t dg, bool valid) {
   return m;
 }
 
-// Each wave owns RS_ITEMS*64 consecutive keys of the tile; ranks are stable.
-__global__ void k_rs_scatter(const uint64_t* kin, const int32_t* vin, uint64_t* kout,
+// Each wave owns ITEMS * 64 consecutive keys of the tile; ranks are stable.
+template <class K, int ITEMS, bool SELF>
+__global__ void k_rs_scatter(const K* kin, const int32_t* vin, K* kout,
                              int32_t* vout, int32_t n, int shift, const int32_t* offs, int ntiles) {
   __shared__ uint32_t cnt[RS_WAVES][256];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int i = threadIdx.x; i < RS_WAVES * 256; i += blockDim.x) (&cnt[0][0])[i] = 0;
   __syncthreads();
-  const int64_t wbase = (int64_t)blockIdx.x * RS_TILE + (int64_t)w * (RS_ITEMS * 64);
+  const int64_t wbase = (int64_t)blockIdx.x * (RS_T * ITEMS) + (int64_t)w * (ITEMS * 64);
   const uint64_t lt = (1ull << lane) - 1ull;
-  for (int s = 0; s < RS_ITEMS; ++s) {
+  for (int s = 0; s < ITEMS; ++s) {
     int64_t i = wbase + s * 64 + lane;
     bool valid = i < n;
     uint32_t dg = valid ? ((uint32_t)(kin[i] >> shift) & 255u) : 0u;
@@ -289,8 +354,33 @@ __global__ void k_rs_scatter(const uint64_t* kin, const int32_t* vin, uint64_t* 
     if (valid && (peers & lt) == 0) cnt[w][dg] += (uint32_t)__popcll(peers);
   }
   __syncthreads();
-  for (int dg = threadIdx.x; dg < 256; dg += blockDim.x) {
-    uint32_t run = (uint32_t)offs[(size_t)dg * ntiles + blockIdx.x];
+  {
+    static_assert(RS_T == 256, "a thread per digit");
+    const int dg = threadIdx.x;
+    uint32_t run = 0;
+    if constexpr (SELF) {
+      // keys of smaller digits anywhere, and of this one in earlier tiles
+      uint32_t all = 0;
+#pragma unroll 8
+      for (int k = 0; k < ntiles; ++k) {
+        const uint32_t c = (uint32_t)offs[(size_t)k * 256 + dg];
+        all += c;
+        run += k < (int)blockIdx.x ? c : 0u;
+      }
+      __shared__ uint32_t wsum[RS_WAVES];
+      uint32_t inc = all;
+#pragma unroll
+      for (int st = 1; st < 64; st <<= 1) {
+        const uint32_t up = __shfl_up(inc, st);
+        if (lane >= st) inc += up;
+      }
+      if (lane == 63) wsum[w] = inc;
+      __syncthreads();
+      run += inc - all;
+      for (int k = 0; k < w; ++k) run += wsum[k];
+    } else {
+      run = (uint32_t)offs[(size_t)dg * ntiles + blockIdx.x];
+    }
     for (int ww = 0; ww < RS_WAVES; ++ww) {
       uint32_t c = cnt[ww][dg];
       cnt[ww][dg] = run;
@@ -298,10 +388,10 @@ __global__ void k_rs_scatter(const uint64_t* kin, const int32_t* vin, uint64_t* 
     }
   }
   __syncthreads();
-  for (int s = 0; s < RS_ITEMS; ++s) {
+  for (int s = 0; s < ITEMS; ++s) {
     int64_t i = wbase + s * 64 + lane;
     bool valid = i < n;
-    uint64_t k = valid ? kin[i] : 0ull;
+    K k = valid ? kin[i] : (K)0;
     int32_t val = valid ? vin[i] : 0;
     uint32_t dg = (uint32_t)(k >> shift) & 255u;
     uint64_t peers = digit_peers(dg, valid);
@@ -317,16 +407,26 @@ __global__ void k_rs_scatter(const uint64_t* kin, const int32_t* vin, uint64_t* 
 }
 
 // ------------------------------------------------------------------ binary radix tree
-__device__ __forceinline__ int kdelta(const uint64_t* k, int n, int i, int j) {
+__device__ __forceinline__ int key_clz(uint32_t x) { return __clz((int)x); }
+__device__ __forceinline__ int key_clz(uint64_t x) { return __clzll((long long)x); }
+
+template <class K>
+__device__ __forceinline__ int kdelta(const K* k, int n, int i, int j) {
   if (j < 0 || j >= n) return -1;
-  uint64_t a = k[i], b = k[j];
-  if (a == b) return 64 + __clz((uint32_t)(i ^ j));
-  return __clzll(a ^ b);
+  K a = k[i], b = k[j];
+  if (a == b) return 8 * (int)sizeof(K) + __clz((uint32_t)(i ^ j));
+  return key_clz((K)(a ^ b));
 }
 
-__global__ void k_karras(const uint64_t* keys, int n, BvhNode* nodes, int32_t* leaf_parent) {
+// Node i covers the sorted triangles between i and its other end.  topo[i]:
+// children, parent, other end.  Also clears the node's arrival counter (k_tile)
+// and cut membership (k_cut).
+template <class K>
+__global__ void k_karras(const K* keys, int n, int4* topo, int32_t* leaf_parent, int32_t* arrive, int32_t* member) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n - 1) return;
+  arrive[i] = 0;
+  member[i] = 0;
   int dl = kdelta(keys, n, i, i - 1), dr = kdelta(keys, n, i, i + 1);
   int d = dr > dl ? 1 : -1;
   int dmin = d > 0 ? dl : dr;
@@ -344,120 +444,32 @@ __global__ void k_karras(const uint64_t* keys, int n, BvhNode* nodes, int32_t* l
   } while (t > 1);
   int gamma = i + s * d + (d < 0 ? -1 : 0);
   int lo = i < j ? i : j, hi = i < j ? j : i;
-  int* nd = (int*)&nodes[i].d;
+  int* nd = (int*)&topo[i];
   if (lo == gamma) {
     nd[0] = (int)((uint32_t)gamma | DT_LEAF_BIT);
     leaf_parent[gamma] = i;
   } else {
     nd[0] = gamma;
-    ((int*)&nodes[gamma].d)[2] = i;
+    ((int*)&topo[gamma])[2] = i;
   }
   if (hi == gamma + 1) {
     nd[1] = (int)((uint32_t)(gamma + 1) | DT_LEAF_BIT);
     leaf_parent[gamma + 1] = i;
   } else {
     nd[1] = gamma + 1;
-    ((int*)&nodes[gamma + 1].d)[2] = i;
+    ((int*)&topo[gamma + 1])[2] = i;
   }
-  nd[3] = 0;
+  nd[3] = j;
   if (i == 0) nd[2] = -1;
-}
-
-__device__ __forceinline__ void put_box(BvhNode* P, int slot, v3 lo, v3 hi) {
-  float* fp = (float*)P + slot * 6;
-  fp[0] = lo.x;
-  fp[1] = lo.y;
-  fp[2] = lo.z;
-  fp[3] = hi.x;
-  fp[4] = hi.y;
-  fp[5] = hi.z;
 }
 
 __device__ __forceinline__ v3 vmin(v3 a, v3 b) { return {fminf(a.x, b.x), fminf(a.y, b.y), fminf(a.z, b.z)}; }
 __device__ __forceinline__ v3 vmax(v3 a, v3 b) { return {fmaxf(a.x, b.x), fmaxf(a.y, b.y), fmaxf(a.z, b.z)}; }
 
-// Order-preserving map of floats to ints (for integer atomic min / max).
+// Order-preserving map of floats to ints.
 __device__ __forceinline__ int fenc(float f) {
   int i = __float_as_int(f);
   return i >= 0 ? i : i ^ 0x7FFFFFFF;
-}
-__device__ __forceinline__ float fdec(int i) { return __int_as_float(i >= 0 ? i : i ^ 0x7FFFFFFF); }
-
-// box accumulators empty, arrival counters and k_cut's membership masks zero
-__global__ void k_fit_init(int* acc, int32_t* arrive, int32_t* member, int n_nodes) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < 6 * (int64_t)n_nodes;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    acc[i] = (i % 6) < 3 ? fenc(INFINITY) : fenc(-INFINITY);
-    if (i < n_nodes) {
-      arrive[i] = 0;
-      member[i] = 0;
-    }
-  }
-}
-
-// Boxes are fitted bottom-up from the triangles in Morton order.
-// Each child writes its box into its slot of the parent node (read only by
-// later kernels) and merges it into the parent's union accumulator with
-// device-scope atomic min / max.  The second child to arrive (arrival
-// counter) reads the finished union back with device-scope atomic loads and
-// carries on upward.  No memory fence is needed: the accumulator is only
-// touched by atomics, which are coherent across the chip, and a wait for
-// their completion orders them before the arrival increment.
-__global__ void k_fit(const float* V, const int32_t* F, int32_t nv, const int32_t* sorted, int n,
-                      BvhNode* nodes, const int32_t* leaf_parent, int32_t* arrive, int* acc,
-                      float4* leaves) {
-  int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n) return;
-  int f = sorted[j];
-  v3 a = load3(V + 3 * vclamp(F[3 * f], nv)), b = load3(V + 3 * vclamp(F[3 * f + 1], nv));
-  v3 c = load3(V + 3 * vclamp(F[3 * f + 2], nv));
-  if (n == 1) {  // no tree: the one leaf (k_wide_write writes them otherwise)
-    leaves[0] = make_float4(a.x, a.y, a.z, __int_as_float(f));
-    leaves[1] = make_float4(b.x, b.y, b.z, 0.f);
-    leaves[2] = make_float4(c.x, c.y, c.z, 0.f);
-    return;
-  }
-  v3 lo = vmin(vmin(a, b), c), hi = vmax(vmax(a, b), c);
-  int ref = (int)((uint32_t)j | DT_LEAF_BIT);
-  int p = leaf_parent[j];
-  // a binary radix tree over 63-bit keys + 31-bit indices is at most 95 deep
-  for (int guard = 0; guard < 256 && p >= 0 && p < n - 1; ++guard) {
-    BvhNode* P = &nodes[p];
-    const int* pd = (const int*)&P->d;
-    int slot = pd[0] == ref ? 0 : 1;
-    put_box(P, slot, lo, hi);
-    int* ac = acc + 6 * p;
-    __hip_atomic_fetch_min(ac + 0, fenc(lo.x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_fetch_min(ac + 1, fenc(lo.y), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_fetch_min(ac + 2, fenc(lo.z), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_fetch_max(ac + 3, fenc(hi.x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_fetch_max(ac + 4, fenc(hi.y), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_fetch_max(ac + 5, fenc(hi.z), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __builtin_amdgcn_s_waitcnt(0);  // the merges above are performed before the arrival below
-    int old = __hip_atomic_fetch_add(&arrive[p], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (old == 0) return;
-    lo = mk3(fdec(__hip_atomic_load(ac + 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)),
-             fdec(__hip_atomic_load(ac + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)),
-             fdec(__hip_atomic_load(ac + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
-    hi = mk3(fdec(__hip_atomic_load(ac + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)),
-             fdec(__hip_atomic_load(ac + 4, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)),
-             fdec(__hip_atomic_load(ac + 5, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
-    if (p == 0) return;
-    ref = p;
-    p = pd[2];
-  }
-}
-
-// 1 for an internal node at even depth (root = 0), else 0: walk to the root
-__global__ void k_even(int32_t n_int, const BvhNode* nodes, int32_t* flag) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_int) return;
-  int dep = 0, p = i;
-  while (p > 0 && p < n_int && dep < 4096) {
-    p = nodes[p].d.z;
-    ++dep;
-  }
-  flag[i] = (dep & 1) == 0;
 }
 
 // ------------------------------------------------------------------ treelet restructuring
@@ -483,121 +495,299 @@ __device__ __forceinline__ float tarea(const TBox& b) {
   v3 e = vmax(b.hi - b.lo, mk3(0.f, 0.f, 0.f));
   return 2.f * (e.x * e.y + e.y * e.z + e.z * e.x);
 }
-__device__ __forceinline__ TBox get_box(const BvhNode& n, int slot) {
-  const float* fp = (const float*)&n + slot * 6;
-  return {mk3(fp[0], fp[1], fp[2]), mk3(fp[3], fp[4], fp[5])};
+__device__ __forceinline__ TBox read_box(const float* p) {
+  return {mk3(p[0], p[1], p[2]), mk3(p[3], p[4], p[5])};
+}
+__device__ __forceinline__ void write_box(float* p, const TBox& b) {
+  p[0] = b.lo.x;
+  p[1] = b.lo.y;
+  p[2] = b.lo.z;
+  p[3] = b.hi.x;
+  p[4] = b.hi.y;
+  p[5] = b.hi.z;
+}
+__device__ __forceinline__ TBox get_box(const BvhNode& n, int slot) { return read_box((const float*)&n + slot * 6); }
+
+// nodes in device memory, as treelet_root sees them: child references, the two
+// child boxes (12 floats), and the parent link
+struct GlobalNodes {
+  BvhNode* n;
+  __device__ __forceinline__ int* kids(int i) const { return (int*)&n[i].d; }
+  __device__ __forceinline__ float* boxes(int i) const { return (float*)&n[i]; }
+  __device__ __forceinline__ void set_up(int i, int parent) const { ((int*)&n[i].d)[2] = parent; }
+};
+
+template <class N>
+__device__ __forceinline__ void set_node(const N& A, int i, int c0, const TBox& b0, int c1, const TBox& b1) {
+  write_box(A.boxes(i), b0);
+  write_box(A.boxes(i) + 6, b1);
+  A.kids(i)[0] = c0;
+  A.kids(i)[1] = c1;
 }
 
-// node i gets children (c0, b0), (c1, b1); with_parent: also its parent link
-__device__ __forceinline__ void set_node(BvhNode* nodes, int i, int c0, const TBox& b0, int c1,
-                                         const TBox& b1, bool with_parent, int parent) {
-  BvhNode* P = &nodes[i];
-  put_box(P, 0, b0.lo, b0.hi);
-  put_box(P, 1, b1.lo, b1.hi);
-  int* pd = (int*)&P->d;
-  pd[0] = c0;
-  pd[1] = c1;
-  if (with_parent) pd[2] = parent;
+template <class N>
+__device__ __forceinline__ void set_parent(const N& A, int ref, int parent) {
+  if (!((uint32_t)ref & DT_LEAF_BIT)) A.set_up(ref, parent);  // triangles keep no link
 }
 
-__device__ __forceinline__ void set_parent(BvhNode* nodes, int32_t* leaf_parent, int ref, int parent) {
-  if ((uint32_t)ref & DT_LEAF_BIT)
-    leaf_parent[(uint32_t)ref & ~DT_LEAF_BIT] = parent;
-  else
-    ((int*)&nodes[ref].d)[2] = parent;
-}
-
-__global__ void k_treelet(int32_t n_int, BvhNode* nodes, int32_t* leaf_parent, const int32_t* even,
-                          int want_even) {
-  const int X = blockIdx.x * blockDim.x + threadIdx.x;
-  if (X >= n_int || (even[X] != 0) != (want_even != 0)) return;
-  int ref[4], inner[3];
-  TBox box[4];
-  int n = 0, m = 1;
-  inner[0] = X;
-  {
-    const BvhNode nx = nodes[X];
-    const int* xd = (const int*)&nx.d;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int c = xd[k];
-      if ((uint32_t)c & DT_LEAF_BIT) {
-        ref[n] = c;
-        box[n++] = get_box(nx, k);
-      } else {
-        inner[m++] = c;
-        const BvhNode nc = nodes[c];
-        const int* cd = (const int*)&nc.d;
-        ref[n] = cd[0];
-        box[n++] = get_box(nc, 0);
-        ref[n] = cd[1];
-        box[n++] = get_box(nc, 1);
-      }
-    }
-  }
-  if (n < 3) return;
+template <class N>
+__device__ __forceinline__ void treelet_root(const N& A, int X) {
+  const int k0 = A.kids(X)[0], k1 = A.kids(X)[1];
+  const bool leaf0 = ((uint32_t)k0 & DT_LEAF_BIT) != 0u, leaf1 = ((uint32_t)k1 & DT_LEAF_BIT) != 0u;
+  if (leaf0 && leaf1) return;
   // candidate topologies, costs = summed areas of the inner nodes below X
-  if (n == 3) {
-    // ((a b) c): the pair with the least box area
-    int bi = 0, bj = 1, bk = 2;
-    float best = tarea(tunion(box[0], box[1]));
-    float c02 = tarea(tunion(box[0], box[2])), c12 = tarea(tunion(box[1], box[2]));
-    if (c02 < best) { best = c02; bi = 0; bj = 2; bk = 1; }
-    if (c12 < best) { best = c12; bi = 1; bj = 2; bk = 0; }
-    const int P1 = inner[1];
-    // current shape: X's internal child holds the pair
-    const TBox pb = tunion(box[bi], box[bj]);
-    set_node(nodes, P1, ref[bi], box[bi], ref[bj], box[bj], true, X);
-    set_node(nodes, X, P1, pb, ref[bk], box[bk], false, 0);
-    set_parent(nodes, leaf_parent, ref[bi], P1);
-    set_parent(nodes, leaf_parent, ref[bj], P1);
-    set_parent(nodes, leaf_parent, ref[bk], X);
+  if (leaf0 || leaf1) {
+    // three leaves, P1's two and X's own: ((a b) c), the pair with the least box area
+    const int P1 = leaf0 ? k1 : k0, r2 = leaf0 ? k0 : k1;
+    const int r0 = A.kids(P1)[0], r1 = A.kids(P1)[1];
+    const TBox b0 = read_box(A.boxes(P1)), b1 = read_box(A.boxes(P1) + 6);
+    const TBox b2 = read_box(A.boxes(X) + (leaf0 ? 0 : 6));
+    const float c01 = tarea(tunion(b0, b1)), c02 = tarea(tunion(b0, b2)), c12 = tarea(tunion(b1, b2));
+    if (!(c02 < c01) && !(c12 < c01)) return;  // already the best
+    const bool with0 = !(c12 < c02);           // the pair is (0 2), else (1 2)
+    const int rp = with0 ? r0 : r1, rs = with0 ? r1 : r0;
+    const TBox bp = with0 ? b0 : b1, bs = with0 ? b1 : b0;
+    set_node(A, P1, rp, bp, r2, b2);
+    set_node(A, X, P1, tunion(bp, b2), rs, bs);
+    set_parent(A, rs, X);
+    set_parent(A, r2, P1);
     return;
   }
   // four leaves: 3 balanced trees ((a b)(c d)) and 12 chains (((a b) c) d)
-  float pa[4][4];
+  uint32_t code;  // a | b << 2 | c << 4 | d << 6 | chain << 8
+  {
+    const TBox box[4] = {read_box(A.boxes(k0)), read_box(A.boxes(k0) + 6), read_box(A.boxes(k1)),
+                         read_box(A.boxes(k1) + 6)};
+    float pa[4][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = i + 1; j < 4; ++j) pa[i][j] = tarea(tunion(box[i], box[j]));
-  // the current tree is balanced with pairs (0 1)(2 3)
-  float best = pa[0][1] + pa[2][3];
-  int kind = 0, a = 0, b = 1, c = 2, d = 3;
-  if (pa[0][2] + pa[1][3] < best) { best = pa[0][2] + pa[1][3]; kind = 0; a = 0; b = 2; c = 1; d = 3; }
-  if (pa[0][3] + pa[1][2] < best) { best = pa[0][3] + pa[1][2]; kind = 0; a = 0; b = 3; c = 1; d = 2; }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = i + 1; j < 4; ++j)
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (k == i || k == j) continue;
-        const int l = 6 - i - j - k;
-        const float cost = pa[i][j] + tarea(tunion(tunion(box[i], box[j]), box[k]));
-        if (cost < best) { best = cost; kind = 1; a = i; b = j; c = k; d = l; }
+      for (int j = i + 1; j < 4; ++j) pa[i][j] = tarea(tunion(box[i], box[j]));
+    constexpr auto pack = [](int a, int b, int c, int d, int chain) -> uint32_t {
+      return (uint32_t)(a | (b << 2) | (c << 4) | (d << 6) | (chain << 8));
+    };
+    // the current tree is balanced with pairs (0 1)(2 3)
+    float best = pa[0][1] + pa[2][3];
+    code = pack(0, 1, 2, 3, 0);
+    auto offer = [&](float cost, uint32_t c) {
+      if (cost < best) {
+        best = cost;
+        code = c;
       }
-  if (kind == 0 && a == 0 && b == 1) return;  // already the best
-  const int P1 = inner[1], P2 = inner[2];
-  const TBox ab = tunion(box[a], box[b]);
-  if (kind == 0) {
-    const TBox cd = tunion(box[c], box[d]);
-    set_node(nodes, P1, ref[a], box[a], ref[b], box[b], true, X);
-    set_node(nodes, P2, ref[c], box[c], ref[d], box[d], true, X);
-    set_node(nodes, X, P1, ab, P2, cd, false, 0);
-    set_parent(nodes, leaf_parent, ref[a], P1);
-    set_parent(nodes, leaf_parent, ref[b], P1);
-    set_parent(nodes, leaf_parent, ref[c], P2);
-    set_parent(nodes, leaf_parent, ref[d], P2);
-  } else {
-    const TBox abc = tunion(ab, box[c]);
-    set_node(nodes, P2, ref[a], box[a], ref[b], box[b], true, P1);
-    set_node(nodes, P1, P2, ab, ref[c], box[c], true, X);
-    set_node(nodes, X, P1, abc, ref[d], box[d], false, 0);
-    set_parent(nodes, leaf_parent, ref[a], P2);
-    set_parent(nodes, leaf_parent, ref[b], P2);
-    set_parent(nodes, leaf_parent, ref[c], P1);
-    set_parent(nodes, leaf_parent, ref[d], X);
+    };
+    offer(pa[0][2] + pa[1][3], pack(0, 2, 1, 3, 0));
+    offer(pa[0][3] + pa[1][2], pack(0, 3, 1, 2, 0));
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = i + 1; j < 4; ++j)
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (k != i && k != j)
+            offer(pa[i][j] + tarea(tunion(tunion(box[i], box[j]), box[k])), pack(i, j, k, 6 - i - j - k, 1));
+    if (code == pack(0, 1, 2, 3, 0)) return;  // already the best
   }
+  // the chosen order's leaves, read again where they lie (indexing the arrays
+  // above would put them in scratch memory)
+  int r[4];
+  TBox b[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int k = (int)((code >> (2 * q)) & 3u), in = k < 2 ? k0 : k1;
+    r[q] = A.kids(in)[k & 1];
+    b[q] = read_box(A.boxes(in) + 6 * (k & 1));
+  }
+  const TBox ab = tunion(b[0], b[1]);
+  if (code < 256u) {
+    const TBox cd = tunion(b[2], b[3]);
+    set_node(A, k0, r[0], b[0], r[1], b[1]);
+    set_node(A, k1, r[2], b[2], r[3], b[3]);
+    set_node(A, X, k0, ab, k1, cd);
+    set_parent(A, r[0], k0);
+    set_parent(A, r[1], k0);
+    set_parent(A, r[2], k1);
+    set_parent(A, r[3], k1);
+  } else {
+    const TBox abc = tunion(ab, b[2]);
+    set_node(A, k1, r[0], b[0], r[1], b[1]);
+    set_node(A, k0, k1, ab, r[2], b[2]);
+    set_node(A, X, k0, abc, r[3], b[3]);
+    A.set_up(k1, k0);
+    set_parent(A, r[0], k1);
+    set_parent(A, r[1], k1);
+    set_parent(A, r[2], k0);
+    set_parent(A, r[3], X);
+  }
+}
+
+// ------------------------------------------------------------------ box fit and treelets, a tile at a time
+// A block takes TILE consecutive sorted triangles and every binary node whose
+// range lies among them (a "local" node: all but a percent or two).  Their boxes are
+// fitted bottom-up and their treelets restructured in LDS, where a step up the
+// tree or a pass costs tens of cycles; through device memory the same work was
+// one atomic round trip across the chip per level and two launches per pass
+// (fit and four passes: 145 us at 102,400 faces, 1.9 ms at 2 M; this kernel with
+// k_top_*: 79 and 420 us).  Threads that come out of the tile's local subtrees carry on
+// up the nodes that span tiles: a child writes its box into its slot of the
+// parent and counts itself in; the second to arrive reads the first one's box and
+// goes on.  Both move the boxes with relaxed agent-scope atomics, which are
+// coherent across the chip, and a wait for their completion orders them before the
+// arrival increment, so no device-wide fence is needed.
+constexpr int TILE = 512;  // 32 KB of LDS, one node per thread
+
+struct TileNodes {
+  float box[TILE][12];
+  int2 kids[TILE];
+  int32_t up[TILE];       // parent if it is local too, else -2 - parent
+  int32_t arrived[TILE];  // children fitted; -1: not a local node
+  uint16_t list[TILE];    // the pass's treelet roots
+  int32_t listed[2];      // how many (passes alternate)
+};
+
+struct LdsNodes {
+  TileNodes* t;
+  int base;
+  __device__ __forceinline__ int* kids(int i) const { return (int*)&t->kids[i - base]; }
+  __device__ __forceinline__ float* boxes(int i) const { return t->box[i - base]; }
+  __device__ __forceinline__ void set_up(int i, int parent) const { t->up[i - base] = parent; }
+};
+
+// flag[i]: -1 for a local node, else 0 (k_top_parity then overwrites it).
+// WAVES per SIMD: a grid of many tiles a CU gains more from a third and fourth
+// resident block (8: 64 registers, some spilled) than it loses (2 M faces 449 ->
+// 351 us); with a tile or two a CU it only loses (102,400 faces 56 -> 66 us).
+constexpr int TILE_CROWD = 512;  // tiles from which 8 waves a SIMD are taken: two per CU
+template <int WAVES>
+__global__ void __launch_bounds__(TILE, WAVES) k_tile(const float* V, const int32_t* F, int32_t nv, const int32_t* sorted,
+                                               int n, const int4* topo, const int32_t* leaf_parent,
+                                               BvhNode* nodes, int32_t* arrive, int32_t* flag,
+                                               float4* leaves) {
+  __shared__ __align__(16) TileNodes T;
+  const int n_int = n - 1, base = blockIdx.x * TILE, t = threadIdx.x, i = base + t;
+  if (n == 1) {  // no tree: the one leaf (k_wide_write writes them otherwise)
+    if (t == 0) {
+      const int f = sorted[0];
+      const v3 a = load3(V + 3 * vclamp(F[3 * f], nv)), b = load3(V + 3 * vclamp(F[3 * f + 1], nv));
+      const v3 c = load3(V + 3 * vclamp(F[3 * f + 2], nv));
+      leaves[0] = make_float4(a.x, a.y, a.z, __int_as_float(f));
+      leaves[1] = make_float4(b.x, b.y, b.z, 0.f);
+      leaves[2] = make_float4(c.x, c.y, c.z, 0.f);
+    }
+    return;
+  }
+  auto in_tile = [&](int k) { return (uint32_t)(k - base) < (uint32_t)TILE; };
+  // node i is local if its whole range (from i to topo.w) lies in the tile
+  const int4 link = i < n_int ? topo[i] : make_int4(0, 0, -1, -1);
+  const bool loc = i < n_int && in_tile(link.w);
+  T.kids[t] = make_int2(link.x, link.y);
+  T.arrived[t] = loc ? 0 : -1;
+  if (t < 2) T.listed[t] = 0;
+  __syncthreads();
+  auto local = [&](int k) { return in_tile(k) && T.arrived[k - base] >= 0; };
+  const bool up_local = link.z >= 0 && local(link.z);
+  T.up[t] = up_local ? link.z : -2 - link.z;
+  // this thread's triangle, and whether its parent is local
+  TBox box = {mk3(0.f, 0.f, 0.f), mk3(0.f, 0.f, 0.f)};
+  int ref = 0, up = -1;  // up: where the climb goes on, encoded as T.up; -1: nowhere
+  if (i < n) {
+    const int f = sorted[i];
+    const v3 a = load3(V + 3 * vclamp(F[3 * f], nv)), b = load3(V + 3 * vclamp(F[3 * f + 1], nv));
+    const v3 c = load3(V + 3 * vclamp(F[3 * f + 2], nv));
+    box = {vmin(vmin(a, b), c), vmax(vmax(a, b), c)};
+    ref = (int)((uint32_t)i | DT_LEAF_BIT);
+    const int p = leaf_parent[i];
+    up = local(p) ? p : -2 - p;
+  }
+  __syncthreads();
+  while (up >= 0) {
+    const int s = up - base;
+    write_box(T.box[s] + (T.kids[s].x == ref ? 0 : 6), box);
+    __threadfence_block();
+    if (atomicAdd(&T.arrived[s], 1) == 0) {
+      up = -1;
+      break;
+    }
+    __threadfence_block();
+    box = tunion(read_box(T.box[s]), read_box(T.box[s] + 6));
+    ref = up;
+    up = T.up[s];
+  }
+  __syncthreads();
+  for (int pass = 0; pass < TILE_PASSES; ++pass) {
+    // the treelet roots: local nodes of one parity of the depth below their
+    // subtree's root that are not a pair of triangles, about a third of the
+    // nodes, listed so that full waves work on them
+    int d = 0;
+    if (loc)
+      for (int k = T.up[t]; k >= 0 && d < TILE; k = T.up[k - base]) ++d;
+    const bool act = loc && (d & 1) == (pass & 1) && ((uint32_t)(T.kids[t].x & T.kids[t].y) & DT_LEAF_BIT) == 0u;
+    const uint64_t m = __ballot(act);
+    int at = 0;
+    if ((t & 63) == 0 && m) at = atomicAdd(&T.listed[pass & 1], __popcll(m));
+    at = __shfl(at, 0);
+    if (act) T.list[at + __popcll(m & ((1ull << (t & 63)) - 1ull))] = (uint16_t)t;
+    __syncthreads();
+    if (t < T.listed[pass & 1]) treelet_root(LdsNodes{&T, base}, base + (int)T.list[t]);
+    if (t == 0) T.listed[1 - (pass & 1)] = 0;
+    __syncthreads();
+  }
+  // local nodes whole; of the others the links (their boxes come from below)
+  if (i < n_int) {
+    const int z = T.up[t];
+    nodes[i].d = make_int4(T.kids[t].x, T.kids[t].y, z >= 0 ? z : -2 - z, link.w);
+    flag[i] = loc ? -1 : 0;
+  }
+  for (int c = t; c < 3 * TILE; c += TILE) {
+    const int s = c / 3, part = c - 3 * s;
+    if (base + s < n_int && T.arrived[s] >= 0)
+      ((float4*)&nodes[base + s])[part] = *(const float4*)(T.box[s] + 4 * part);
+  }
+  // a binary radix tree over 64-bit keys and 31-bit indices is at most 95 deep
+  int p = -2 - up;
+  for (int guard = 0; guard < 256 && p >= 0 && p < n_int; ++guard) {
+    const int4 at = topo[p];
+    const int slot = at.x == ref ? 0 : 1;
+    unsigned long long* mine = (unsigned long long*)((float*)&nodes[p] + 6 * slot);
+    unsigned long long* other = (unsigned long long*)((float*)&nodes[p] + 6 * (1 - slot));
+    const float v[6] = {box.lo.x, box.lo.y, box.lo.z, box.hi.x, box.hi.y, box.hi.z};
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      __hip_atomic_store(mine + k, (unsigned long long)__float_as_uint(v[2 * k]) |
+                                       ((unsigned long long)__float_as_uint(v[2 * k + 1]) << 32),
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the box is out before the arrival below
+    if (__hip_atomic_fetch_add(&arrive[p], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) break;
+    float w[6];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const unsigned long long x = __hip_atomic_load(other + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      w[2 * k] = __uint_as_float((uint32_t)x);
+      w[2 * k + 1] = __uint_as_float((uint32_t)(x >> 32));
+    }
+    box = tunion(box, read_box(w));
+    ref = p;
+    p = at.z;
+  }
+}
+
+// Treelet passes over the nodes that span tiles (flag >= 0), whose treelets
+// reach into the local subtrees' tops: the depth parity (root = 0) by a walk to
+// the root, then the restructuring of one parity's treelets
+__global__ void k_top_parity(int32_t n_int, const BvhNode* nodes, int32_t* flag) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n_int || flag[i] < 0) return;
+  int dep = 0, p = i;
+  while (p > 0 && p < n_int && dep < 4096) {
+    p = nodes[p].d.z;
+    ++dep;
+  }
+  flag[i] = dep & 1;
+}
+
+__global__ void k_top_treelet(int32_t n_int, BvhNode* nodes, const int32_t* flag, int parity) {
+  const int X = blockIdx.x * blockDim.x + threadIdx.x;
+  if (X >= n_int || flag[X] != parity) return;
+  treelet_root(GlobalNodes{nodes}, X);
 }
 
 // Exponent e of the quantization step 2^e of one axis of a node box [lo, hi]:
@@ -877,15 +1067,6 @@ __global__ void __launch_bounds__(CUT_T) k_wide_write(const float* V, const int3
   ((uint4*)(out + w))[sub] = v;
 }
 
-__global__ void k_header(BvhHeader* hdr, int32_t nv, int32_t nf) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    hdr->nv = nv;
-    hdr->nf = nf;
-    hdr->depth = nf == 1 ? 1 : 0;  // larger trees: k_wide_roots
-    hdr->pad0 = 0;
-  }
-}
-
 __global__ void k_copy_vn(const float4* vn, int32_t nv, float* N) {
   int v = blockIdx.x * blockDim.x + threadIdx.x;
   if (v >= nv) return;
@@ -904,13 +1085,13 @@ struct BuildWs {
   int32_t* arrive;
   int* acc;
   int32_t *flag, *member;
-  int32_t *vcnt, *cursor;
+  int32_t* vcnt;
 };
 
-int rs_tiles(int32_t nf) { return (int)((nf + RS_TILE - 1) / RS_TILE); }
+int rs_tiles(int32_t nf, int items) { return (int)((nf + RS_T * items - 1) / (RS_T * items)); }
 
 size_t carve_build(Carver& c, int32_t nv, int32_t nf, BuildWs* w) {
-  int nt = rs_tiles(nf);
+  int nt = rs_tiles(nf, RS_ITEMS);
   BuildWs x;
   x.k0 = c.take<uint64_t>(nf);
   x.k1 = c.take<uint64_t>(nf);
@@ -924,7 +1105,7 @@ size_t carve_build(Carver& c, int32_t nv, int32_t nf, BuildWs* w) {
   x.flag = c.take<int32_t>(nf);
   x.member = c.take<int32_t>(nf);
   x.vcnt = c.take<int32_t>(nv);
-  x.cursor = c.take<int32_t>(nv);
+  c.take<int32_t>(nv);  // spare: the workspace a mesh needs decides what dt_build_bvh_noalloc takes
   if (w) *w = x;
   return c.used();
 }
@@ -943,14 +1124,19 @@ dt_status dt_fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t s) {
 
 size_t dt_scan_partials_count() { return SCAN_NB + 1; }
 
-// out[0..n) = exclusive prefix sums of in[0..n); partials[SCAN_NB] = total.
-// in == out is allowed.
+// out[0..n) = exclusive prefix sums of in[0..n); partials[SCAN_NB] = total,
+// also to *total if given.  in == out is allowed.
 template <class T>
-static dt_status scan_exclusive(const T* in, T* out, int32_t n, T* partials, hipStream_t s) {
+static dt_status scan_exclusive(const T* in, T* out, int32_t n, T* partials, T* total, hipStream_t s) {
   if (n <= 0) return DT_OK;
+  if (n <= SCAN_ONE_MAX) {
+    hipLaunchKernelGGL(k_scan_one<T>, dim3(1), dim3(SCAN_ONE_T), 0, s, in, out, n, partials, total);
+    DT_CHECK_LAUNCH();
+    return DT_OK;
+  }
   int32_t chunk = (n + SCAN_NB - 1) / SCAN_NB;
   hipLaunchKernelGGL(k_scan_reduce<T>, dim3(SCAN_NB), dim3(SCAN_T), 0, s, in, n, chunk, partials);
-  hipLaunchKernelGGL(k_scan_partials<T>, dim3(1), dim3(SCAN_NB), 0, s, partials, SCAN_NB);
+  hipLaunchKernelGGL(k_scan_partials<T>, dim3(1), dim3(SCAN_NB), 0, s, partials, SCAN_NB, total);
   hipLaunchKernelGGL(k_scan_apply<T>, dim3(SCAN_NB), dim3(SCAN_T), 0, s, in, out, n, chunk, partials);
   DT_CHECK_LAUNCH();
   return DT_OK;
@@ -958,7 +1144,39 @@ static dt_status scan_exclusive(const T* in, T* out, int32_t n, T* partials, hip
 
 dt_status dt_scan_exclusive_i32(const int32_t* in, int32_t* out, int32_t n, int32_t* partials,
                                 hipStream_t s) {
-  return scan_exclusive(in, out, n, partials, s);
+  return scan_exclusive(in, out, n, partials, (int32_t*)nullptr, s);
+}
+
+// stable LSD radix sort of (Morton key, face) in passes of 8 bits, then the
+// binary radix tree over the sorted keys; *order: the sorted faces
+template <class K, int ITEMS>
+static dt_status sort_and_link(const float* V, const int32_t* F, int32_t nf, int32_t nv, int drop, const BuildWs& w,
+                               int32_t* hist, BvhHeader* hdr, int4* topo, int32_t* lpar, int32_t** order,
+                               hipStream_t s) {
+  K *ki = (K*)w.k0, *ko = (K*)w.k1;
+  int32_t *vi = w.v0, *vo = w.v1;
+  const int nt = rs_tiles(nf, ITEMS);
+  hipLaunchKernelGGL(k_morton<K>, dim3(dt_blocks(nf, NBB)), dim3(NBB), 0, s, V, F, nf, nv, drop, w.bpart, hdr, ki, vi);
+  for (int shift = 0; shift < 8 * (int)sizeof(K); shift += 8) {
+    constexpr bool SELF = ITEMS < RS_ITEMS;
+    hipLaunchKernelGGL((k_rs_hist<K, ITEMS, SELF>), dim3(nt), dim3(RS_T), 0, s, ki, nf, shift, hist, nt);
+    if (!SELF)
+      if (dt_status st = scan_exclusive(hist, hist, 256 * nt, w.scanp, (int32_t*)nullptr, s)) return st;
+    hipLaunchKernelGGL((k_rs_scatter<K, ITEMS, SELF>), dim3(nt), dim3(RS_T), 0, s, ki, vi, ko, vo, nf, shift, hist, nt);
+    DT_CHECK_LAUNCH();
+    K* tk = ki;
+    ki = ko;
+    ko = tk;
+    int32_t* tv = vi;
+    vi = vo;
+    vo = tv;
+  }
+  if (nf > 1)
+    hipLaunchKernelGGL(k_karras<K>, dim3(dt_blocks(nf - 1, 256)), dim3(256), 0, s, ki, nf, topo, lpar, w.arrive,
+                       w.member);
+  DT_CHECK_LAUNCH();
+  *order = vi;
+  return DT_OK;
 }
 
 // ------------------------------------------------------------------ C ABI
@@ -1001,65 +1219,52 @@ extern "C" dt_status dt_build_bvh(const float* V, int32_t nv, const int32_t* F, 
   int32_t* idx = (int32_t*)(b + L.csr_idx);
   int32_t* lpar = (int32_t*)(b + L.leaf_parent);
 
-  hipLaunchKernelGGL(k_header, dim3(1), dim3(64), 0, s, hdr, nv, nf);
-  // normals (Eq. 12-13)
-  hipLaunchKernelGGL(k_face_normals, dim3(dt_blocks(nf, 256)), dim3(256), 0, s, V, F, nf, nv, fn);
-  if (dt_status st = dt_fill_u32((uint32_t*)w.vcnt, 0u, nv, s)) return st;
-  if (dt_status st = dt_fill_u32((uint32_t*)w.cursor, 0u, nv, s)) return st;
-  hipLaunchKernelGGL(k_vcount, dim3(dt_blocks(nf, 256)), dim3(256), 0, s, F, nf, nv, w.vcnt);
-  if (dt_status st = dt_scan_exclusive_i32(w.vcnt, off, nv, w.scanp, s)) return st;
-  hipLaunchKernelGGL(k_copy_total, dim3(1), dim3(64), 0, s, w.scanp, SCAN_NB, off + nv);
-  hipLaunchKernelGGL(k_vfill, dim3(dt_blocks(nf, 256)), dim3(256), 0, s, F, nf, nv, off, w.cursor,
-                     idx);
-  hipLaunchKernelGGL(k_vsort, dim3(dt_blocks(nv, 256)), dim3(256), 0, s, off, nv, idx);
+  // normals (Eq. 12-13).  The corner ranks sit in the sort's key buffers
+  int32_t* rank = (int32_t*)w.k0;
+  hipLaunchKernelGGL(k_build_init, dim3(dt_blocks(nv, 256)), dim3(256), 0, s, hdr, nv, nf, w.vcnt);
+  hipLaunchKernelGGL(k_faces, dim3(dt_blocks(nf, 256)), dim3(256), 0, s, V, F, nf, nv, fn, w.vcnt, rank);
+  if (dt_status st = scan_exclusive(w.vcnt, off, nv, w.scanp, off + nv, s)) return st;
+  hipLaunchKernelGGL(k_vfill, dim3(dt_blocks(nf, 256)), dim3(256), 0, s, F, nf, nv, off, rank, idx);
   hipLaunchKernelGGL(k_vnormals, dim3(dt_blocks(nv, 256)), dim3(256), 0, s, off, idx, fn, nv, vn);
   DT_CHECK_LAUNCH();
-  // Morton codes of face centroids
+  // Morton order and the binary tree.  Up to 2^23 triangles the top 32 bits of
+  // the code (2,048 cells an axis) order them finely enough (ties fall back to
+  // the face index) and halve the sort: a 2 M face wall's tree has the same
+  // node visits with 64, 32 or 29 bits
   hipLaunchKernelGGL(k_bounds, dim3(NBB), dim3(256), 0, s, V, F, nf, nv, w.bpart);
-  // up to 2^20 triangles the top 32 bits of the code order them finely enough
-  // (ties fall back to the face index) and halve the sort
-  const int key_bits = nf <= (1 << 20) ? 32 : 64;
-  hipLaunchKernelGGL(k_bounds_final, dim3(1), dim3(NBB), 0, s, w.bpart, hdr);
-  hipLaunchKernelGGL(k_morton, dim3(dt_blocks(nf, 256)), dim3(256), 0, s, V, F, nf, nv,
-                     key_bits == 32 ? 31 : 0, hdr, w.k0, w.v0);
-  DT_CHECK_LAUNCH();
-  // stable LSD radix sort of (key, face), passes of 8 bits
-  int nt = rs_tiles(nf);
-  uint64_t *ki = w.k0, *ko = w.k1;
-  int32_t *vi = w.v0, *vo = w.v1;
-  for (int shift = 0; shift < key_bits; shift += 8) {
-    hipLaunchKernelGGL(k_rs_hist, dim3(nt), dim3(RS_T), 0, s, ki, nf, shift, w.hist, nt);
-    if (dt_status st = dt_scan_exclusive_i32(w.hist, w.hist, 256 * nt, w.scanp, s)) return st;
-    hipLaunchKernelGGL(k_rs_scatter, dim3(nt), dim3(RS_T), 0, s, ki, vi, ko, vo, nf, shift, w.hist,
-                       nt);
-    DT_CHECK_LAUNCH();
-    uint64_t* tk = ki;
-    ki = ko;
-    ko = tk;
-    int32_t* tv = vi;
-    vi = vo;
-    vo = tv;
+  int32_t* vi = nullptr;
+  int4* topo = (int4*)w.acc;
+  dt_status st;
+  if (nf >= 1024 && nf <= (1 << 17)) {
+    // smaller tiles (with eight keys a thread a 102,400-key pass has 50 blocks
+    // for 256 CUs) and few enough of them for every block to add up their
+    // histograms: a pass 27 -> 17 us.  The histogram, a word per four keys, sits
+    // where the links go afterwards
+    st = sort_and_link<uint32_t, 4>(V, F, nf, nv, 31, w, (int32_t*)w.acc, hdr, topo, lpar, &vi, s);
+  } else if (nf <= (1 << 23)) {
+    st = sort_and_link<uint32_t, RS_ITEMS>(V, F, nf, nv, 31, w, w.hist, hdr, topo, lpar, &vi, s);
+  } else {
+    st = sort_and_link<uint64_t, RS_ITEMS>(V, F, nf, nv, 0, w, w.hist, hdr, topo, lpar, &vi, s);
   }
-  // tree + boxes
-  if (nf > 1) {
-    hipLaunchKernelGGL(k_karras, dim3(dt_blocks(nf - 1, 256)), dim3(256), 0, s, ki, nf, nodes, lpar);
-    hipLaunchKernelGGL(k_fit_init, dim3(dt_blocks(6 * (int64_t)(nf - 1), 256) < 4096 ?
-                                        dt_blocks(6 * (int64_t)(nf - 1), 256) : 4096),
-                       dim3(256), 0, s, w.acc, w.arrive, w.member, nf - 1);
-  }
-  hipLaunchKernelGGL(k_fit, dim3(dt_blocks(nf, 256)), dim3(256), 0, s, V, F, nv, vi, nf, nodes,
-                     lpar, w.arrive, w.acc, leaves);
-  // treelet restructuring: even-depth roots, then odd, twice
-  if (nf > 2) {
-    for (int pass = 0; pass < TREELET_PASSES; ++pass) {
-      hipLaunchKernelGGL(k_even, dim3(dt_blocks(nf - 1, 256)), dim3(256), 0, s, nf - 1, nodes, w.flag);
-      hipLaunchKernelGGL(k_treelet, dim3(dt_blocks(nf - 1, 256)), dim3(256), 0, s, nf - 1, nodes, lpar,
-                         w.flag, (pass & 1) == 0 ? 1 : 0);
+  if (st != DT_OK) return st;
+  // boxes, and treelets restructured
+  const unsigned tiles = dt_blocks(nf, TILE);
+  if (tiles >= TILE_CROWD)
+    hipLaunchKernelGGL(k_tile<8>, dim3(tiles), dim3(TILE), 0, s, V, F, nv, vi, nf, topo, lpar, nodes, w.arrive,
+                       w.flag, leaves);
+  else
+    hipLaunchKernelGGL(k_tile<4>, dim3(tiles), dim3(TILE), 0, s, V, F, nv, vi, nf, topo, lpar, nodes, w.arrive,
+                       w.flag, leaves);
+  if (nf > TILE) {
+    for (int pass = 0; pass < TOP_PASSES; ++pass) {
+      hipLaunchKernelGGL(k_top_parity, dim3(dt_blocks(nf - 1, 256)), dim3(256), 0, s, nf - 1, nodes, w.flag);
+      hipLaunchKernelGGL(k_top_treelet, dim3(dt_blocks(nf - 1, 256)), dim3(256), 0, s, nf - 1, nodes, w.flag,
+                         pass & 1);
     }
   }
   DT_CHECK_LAUNCH();
-  // 6-wide traversal tree.  The box accumulators, the sort's key buffers and the
-  // parity flags are free by now and hold the cuts, the child counts with
+  // 6-wide traversal tree.  The links, the sort's key buffers and the parity flags
+  // are free by now and hold the cuts, the child counts with
   // their prefix sums, and the wide nodes' owners
   if (nf > 1) {
     uint32_t* cut = (uint32_t*)w.acc;
@@ -1070,7 +1275,7 @@ extern "C" dt_status dt_build_bvh(const float* V, int32_t nv, const int32_t* F, 
     const unsigned nb = dt_blocks(nf - 1, CUT_T);
     hipLaunchKernelGGL(k_cut, dim3(nb), dim3(CUT_T), 0, s, nf - 1, nodes, cut, w.member);
     hipLaunchKernelGGL(k_wide_roots, dim3(nb), dim3(CUT_T), 0, s, nf - 1, nodes, cut, w.member, cnt, hdr);
-    if (dt_status st = scan_exclusive(cnt, pre, nf - 1, part, s)) return st;
+    if (dt_status st = scan_exclusive(cnt, pre, nf - 1, part, (unsigned long long*)nullptr, s)) return st;
     hipLaunchKernelGGL(k_wide_owner, dim3(nb), dim3(CUT_T), 0, s, nf - 1, cut, cnt, pre, w.flag, cap);
     hipLaunchKernelGGL(k_wide_write, dim3(dt_blocks(8 * (int64_t)cap, CUT_T)), dim3(CUT_T), 0, s, V, F, nv, nf, vi,
                        nodes, cut, w.member, pre, part + SCAN_NB, w.flag, (WideNode*)(b + L.wide), cap, leaves);
