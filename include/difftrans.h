@@ -347,13 +347,14 @@ dt_status dt_trace_backward(const dt_scene* sc, const dt_rays* rays, const dt_tr
  * large-steps method it cites): solves (I + lambda L) x = b for the three
  * coordinate columns on the device, by Chebyshev iteration over the interval
  * [1, 1 + lambda m] that holds the matrix's eigenvalues (m: the largest
- * d_i + d_j over the edges, an upper bound of L's largest eigenvalue).  adj_off
+ * degree plus mean neighbour degree over the vertices, an upper bound of L's
+ * largest eigenvalue).  adj_off
  * [nv + 1], adj [adj_off[nv]]: each vertex's neighbours along edges (int32,
  * device, each undirected edge listed from both ends, no repeats).  b, x:
  * device float64 [nv][3]; x holds the starting guess on entry and the
  * solution on return.  Stops when every column's residual is within tol of
- * |b| (read back every 16 iterations: this call waits for the device, unlike
- * the others), or after max_iters iterations, returning DT_ERR_NOT_CONVERGED
+ * |b| (read back every 16 iterations from shortly before the iteration that the
+ * interval's bound predicts: this call waits for the device, unlike the others), or after max_iters iterations, returning DT_ERR_NOT_CONVERGED
  * then with x the last iterate.  iters_out, resid_out (HOST, may be NULL): the
  * iterations run and the largest relative residual.  The sums are reduced in
  * a fixed order, so the solve is bit-reproducible. */
