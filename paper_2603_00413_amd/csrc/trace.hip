@@ -604,7 +604,10 @@ struct VtxAdj {
 // Adjoint of node i of generation g: writes its record (subtree radiance,
 // d/d origin, d/d direction) to cur, adds its dIoR / dsigma terms to acc and
 // returns its vertex contributions.
-template <bool GRID, bool FIELD>
+// FIELD: 0 none; 1 the field's ray terms in one pass over the samples, its
+// parameters' gradient (if any) left to k_field_grad; 2 the parameters' gradient
+// added in place (fields whose records exceed the scratch region)
+template <bool GRID, int FIELD>
 __device__ __forceinline__ void adjoint_node(const SceneDev& sc, const Gen& q, int64_t i,
                                              const float* grad_rgb, const Adj& nxt, const Adj& cur,
                                              float4& acc, VtxAdj& out, float4* fseg) {
@@ -614,34 +617,36 @@ __device__ __forceinline__ void adjoint_node(const SceneDev& sc, const Gen& q, i
   int pix = __float_as_int(d4.w);
   v3 gp = load3(grad_rgb + 3 * pix);
   v3 gW = mul3(gp, W);
-  // With fseg, the field parameters' gradient is left to k_field_grad: this
-  // node's exterior segment (radiance beyond it, its upstream gradient, end
-  // and kind) goes to fseg and the backward here takes the ray's terms only.
-  FieldDev fdv = sc.fd;
-  if constexpr (FIELD) {
-    if (fseg) {
-      fdv.d_grid = nullptr;
-      fdv.d_planes = nullptr;
-      fseg[2 * i + 1] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
+  // With fseg, this node's exterior segment (radiance beyond it, its upstream
+  // gradient, end and kind) goes there for k_field_grad
+  if constexpr (FIELD == 1) {
+    if (fseg) fseg[2 * i + 1] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   if (!(code & C_HIT)) {
     if (sc.env.kind != DT_ENV_EQUIRECT) return;  // written by the MLP kernel
     v3 dd;
-    if constexpr (FIELD) {
+    if constexpr (FIELD != 0) {
       if (!(__float_as_uint(w4.w) & RAY_INSIDE)) {
         // L = C + T E along the exterior ray
-        v3 C;
-        float T;
-        field_segment(sc.fd, o, d, 0.f, true, C, T);
-        v3 E = env_equirect_grad(sc.env, d, gW * T, &dd);
-        v3 ob = mk3(0.f, 0.f, 0.f);
+        v3 ob = mk3(0.f, 0.f, 0.f), L;
         float tb = 0.f;
-        const v3 L = C + E * T;
-        field_segment_bwd(fdv, o, d, 0.f, true, L, gW, ob, dd, tb);
-        if (fseg) {
-          fseg[2 * i] = make_float4(L.x, L.y, L.z, 0.f);
-          fseg[2 * i + 1] = make_float4(gW.x, gW.y, gW.z, 2.f);  // open segment
+        if constexpr (FIELD == 1) {
+          FieldSums fs;
+          field_segment_sums(sc.fd, o, d, 0.f, true, gW, fs);
+          const v3 E = env_equirect_grad(sc.env, d, gW * fs.T, &dd);
+          L = fs.C + E * fs.T;
+          field_sums_bwd(sc.fd, d, fs, L, gW, ob, dd, tb);
+          if (fseg) {
+            fseg[2 * i] = make_float4(L.x, L.y, L.z, fs.T);
+            fseg[2 * i + 1] = make_float4(gW.x, gW.y, gW.z, 2.f);  // open segment
+          }
+        } else {
+          v3 C;
+          float T;
+          field_segment(sc.fd, o, d, 0.f, true, C, T);
+          const v3 E = env_equirect_grad(sc.env, d, gW * T, &dd);
+          L = C + E * T;
+          field_segment_bwd(sc.fd, o, d, 0.f, true, L, gW, ob, dd, tb);
         }
         cur.L[i] = make_float4(L.x, L.y, L.z, 0.f);
         cur.O[i] = make_float4(ob.x, ob.y, ob.z, 0.f);
@@ -657,7 +662,7 @@ __device__ __forceinline__ void adjoint_node(const SceneDev& sc, const Gen& q, i
   }
   bool trunc = (code & C_TRUNC) != 0u;
   // with a field, a truncated hit reached from outside still emits its segment
-  const bool field_seg = FIELD && (code & C_ENTER) != 0u;
+  const bool field_seg = FIELD != 0 && (code & C_ENTER) != 0u;
   if (trunc && !sc.terminal_env && !field_seg) {
     cur.L[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     cur.O[i] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -669,8 +674,16 @@ __device__ __forceinline__ void adjoint_node(const SceneDev& sc, const Gen& q, i
   HitGeo geo = load_geo(sc, tri);
   // with the grid, the interior segment's attenuation and its adjoint sums
   // come from one pass over its samples (shade<false> leaves A to it)
-  Shade s = shade<false, FIELD>(sc, geo, o, d, t, b1, b2, code);
+  Shade s = shade<false, FIELD == 2>(sc, geo, o, d, t, b1, b2, code);
   const bool entering = (code & C_ENTER) != 0u, tir = (code & C_TIR) != 0u;
+  FieldSums fs;
+  if constexpr (FIELD == 1) {
+    if (field_seg) {
+      field_segment_sums(sc.fd, o, d, t, false, gW, fs);
+      s.A = mk3(fs.T, fs.T, fs.T);
+      s.Cem = fs.C;
+    }
+  }
   TauSums ts;
   if constexpr (GRID) {
     if (!entering) {
@@ -772,17 +785,21 @@ __device__ __forceinline__ void adjoint_node(const SceneDev& sc, const Gen& q, i
     acc.w += -Abar.z * t * s.A.z;
     tbar += -(Abar.x * sg0 * s.A.x + Abar.y * sg1 * s.A.y + Abar.z * sg2 * s.A.z);
   }
-  if constexpr (FIELD) {
+  if constexpr (FIELD != 0) {
     if (field_seg) {
       // L = C + T M over the exterior segment [0, t]; T's effect on M is in
       // the field's backward (A = T is not used for the attenuation here)
       L = L + s.Cem;
       // the segment's radiance C + T M (A = T here)
       const v3 Lseg = s.Cem + Mf * s.A.x;
-      field_segment_bwd(fdv, o, d, t, false, Lseg, gW, oabs, dbar, tbar);
-      if (fseg) {
-        fseg[2 * i] = make_float4(Lseg.x, Lseg.y, Lseg.z, t);
-        fseg[2 * i + 1] = make_float4(gW.x, gW.y, gW.z, 1.f);  // closed segment [0, t]
+      if constexpr (FIELD == 1) {
+        field_sums_bwd(sc.fd, d, fs, Lseg, gW, oabs, dbar, tbar);
+        if (fseg) {
+          fseg[2 * i] = make_float4(Lseg.x, Lseg.y, Lseg.z, t);
+          fseg[2 * i + 1] = make_float4(gW.x, gW.y, gW.z, 1.f);  // closed segment [0, t]
+        }
+      } else {
+        field_segment_bwd(sc.fd, o, d, t, false, Lseg, gW, oabs, dbar, tbar);
       }
     }
   }
@@ -859,7 +876,7 @@ __device__ __forceinline__ void adjoint_node(const SceneDev& sc, const Gen& q, i
 // hit).
 // (the field's instantiations, whose segment replays hold some 300 registers
 // a lane, are held to 256 so that two waves share a SIMD)
-template <bool GRID, bool FIELD>
+template <bool GRID, int FIELD>
 __global__ void __launch_bounds__(AB, FIELD ? 2 : 1) k_adjoint(SceneDev sc, Gen q, int g, const Counters* ctr,
                                                 const float* grad_rgb, Adj nxt, Adj cur,
                                                 FaceRec* frec, int2* fkey, uint32_t* fcnt,
@@ -1020,7 +1037,7 @@ __global__ void __launch_bounds__(GG_T) k_grid_grad(AbsorbDev G, Gen q, int g, c
 // distinct 2 x 2 texel block among them, lanes 0-11 each sum one tap-channel
 // value over the block's lanes and add it with one atomic.
 __global__ void __launch_bounds__(GG_T) k_env_tex_grad(SceneDev sc, Gen q, int g, const Counters* ctr,
-                                                       const float* grad_rgb) {
+                                                       const float* grad_rgb, const float4* fseg) {
   const EnvDev& e = sc.env;
   __shared__ float taps[GG_T / 64][64][13];  // per wave and lane: 4 taps x 3 channels (+1 pad)
   const int64_t n = ctr->count[g];
@@ -1040,10 +1057,14 @@ __global__ void __launch_bounds__(GG_T) k_env_tex_grad(SceneDev sc, Gen q, int g
         if (sc.fd.grid && ((code & C_HIT) ? (code & C_ENTER) != 0u
                                           : !(__float_as_uint(w4.w) & RAY_INSIDE))) {
           // an exterior segment through the volumetric field: the lookup is
-          // weighted by the field's transmittance
+          // weighted by the field's transmittance, which the adjoint left in
+          // fseg for a miss
           v3 C;
           float T;
-          field_segment(sc.fd, xyz(q.o[i]), d, q.hit[i].x, !(code & C_HIT), C, T);
+          if (fseg && !(code & C_HIT))
+            T = fseg[2 * i].w;
+          else
+            field_segment(sc.fd, xyz(q.o[i]), d, q.hit[i].x, !(code & C_HIT), C, T);
           gb = gb * T;
         }
         if ((code & C_HIT) && !(code & C_ENTER)) {
@@ -1134,11 +1155,14 @@ __global__ void k_grid_gather(const float* copies, int n_copies, int nx, int ny,
 // and one cell of each plane (4 corners), so a sample's contributions are a
 // record of 32 values for its grid cell and 16 for each plane cell.  Waves
 // step through the samples together; per sample the wave parks its lanes'
-// records in LDS and, per distinct cell among them, sums them and adds the
-// sums with one atomic per value into that cell's record (grid records of
+// records in LDS, sorts its lanes by cell and adds the sum over each cell's
+// lanes with one atomic per value into that cell's record (grid records of
 // FG_GREC floats, plane records of FG_PREC), in copy blockIdx.x % copies;
 // k_field_gather turns the records into node values.  Neighbouring rays
-// sample the same cells, so a wave's atomics shrink to a few per cell.
+// sample the same cells, so a wave's atomics shrink to a few per cell.  What is
+// left is bound by them: float atomics are carried out at the memory side, and
+// the kernel's time over the generations is 0.13 ms + 48 us per million
+// requests (6 to 19 million; its arithmetic would take 0.1 ms).
 constexpr int FG_T = 256;
 constexpr int FG_GREC = 32;  // 8 corners x 4 channels
 constexpr int FG_PREC = 16;  // 4 corners x 4 channels
@@ -1149,153 +1173,220 @@ __device__ __forceinline__ size_t field_rec_floats(const FieldDev& F) {
   return (size_t)FG_GREC * (F.nx - 1) * (F.ny - 1) * (F.nz - 1) + 3 * FG_PREC * pc * pc;
 }
 
-constexpr int FG_PARK = 52;  // per lane: up to 48 parked values, then up to 3 keys
+// lane ^ M's value.  Cross-lane moves within 16 lanes ride on the instruction
+// (data-parallel primitives); the others go through the LDS crossbar.
+template <int M>
+__device__ __forceinline__ uint32_t xor_lane(uint32_t v) {
+  const int x = (int)v;
+  if constexpr (M == 1) return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);   // quad 1 0 3 2
+  if constexpr (M == 2) return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true);   // quad 2 3 0 1
+  if constexpr (M == 3) return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x1B, 0xF, 0xF, true);   // quad 3 2 1 0
+  if constexpr (M == 7) return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x141, 0xF, 0xF, true);  // half-row mirror
+  if constexpr (M == 15) return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x140, 0xF, 0xF, true); // row mirror
+  if constexpr (M == 4) return xor_lane<3>(xor_lane<7>(v));
+  if constexpr (M == 8) return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, true);  // row rotate by 8
+  if constexpr (M == 16) return (uint32_t)__builtin_amdgcn_ds_swizzle(x, 0x401F);
+  if constexpr (M == 31) return (uint32_t)__builtin_amdgcn_ds_swizzle(x, 0x7C1F);
+  return (uint32_t)__shfl_xor(x, M);
+}
 
-// the wave's parked grid records (FG_GREC values and a key per lane) summed
-// per distinct key and added to base + key * FG_GREC + value
-__device__ __forceinline__ void merge_grid(float (*park)[FG_PARK], int key, float* base) {
+// the wave's 64 values in ascending order over its lanes (bitonic network: each
+// merge first compares mirrored halves, then strides of half, quarter, ...)
+template <int M, int BIT>
+__device__ __forceinline__ void sort_step(uint32_t& v, int lane) {
+  const uint32_t o = xor_lane<M>(v);
+  v = (lane & BIT) ? max(v, o) : min(v, o);
+}
+__device__ __forceinline__ uint32_t sort64(uint32_t v, int lane) {
+  sort_step<1, 1>(v, lane);
+  sort_step<3, 2>(v, lane);
+  sort_step<1, 1>(v, lane);
+  sort_step<7, 4>(v, lane);
+  sort_step<2, 2>(v, lane);
+  sort_step<1, 1>(v, lane);
+  sort_step<15, 8>(v, lane);
+  sort_step<4, 4>(v, lane);
+  sort_step<2, 2>(v, lane);
+  sort_step<1, 1>(v, lane);
+  sort_step<31, 16>(v, lane);
+  sort_step<8, 8>(v, lane);
+  sort_step<4, 4>(v, lane);
+  sort_step<2, 2>(v, lane);
+  sort_step<1, 1>(v, lane);
+  sort_step<63, 32>(v, lane);
+  sort_step<16, 16>(v, lane);
+  sort_step<8, 8>(v, lane);
+  sort_step<4, 4>(v, lane);
+  sort_step<2, 2>(v, lane);
+  sort_step<1, 1>(v, lane);
+  return v;
+}
+
+// Adds the wave's parked records (VALS values per lane, rows of park STRIDE
+// apart) to base + cell * VALS + value, summed per distinct cell.  order: the
+// wave's (cell << 6 | lane) in ascending order, cells of lanes without a record
+// FG_NONE.  The wave splits into 64 / VALS groups of VALS lanes, one lane per
+// value, and group k walks the k-th VALS entries of the order: its reads depend
+// on nothing but the order, and a sum goes out where the next entry's cell
+// differs.  (Finding each distinct cell by ballots and walking its lanes' bits
+// took a chain of dependent steps per cell: k_field_grad 965 -> 677 us a generation
+// of 2 M nodes, 8 samples.)
+constexpr uint32_t FG_NONE = 0x3FFFFFFu;
+
+template <int VALS, int STRIDE>
+__device__ __forceinline__ void add_sorted(const float* park, const uint32_t* order, float* base) {
+  const int lane = (int)(threadIdx.x & 63u), val = lane % VALS;
+  const uint32_t* mine = order + (lane / VALS) * VALS;
+  float sum = 0.f;
+  uint4 e = *(const uint4*)mine;
+#pragma unroll 2
+  for (int k = 0; k < VALS; k += 4) {
+    uint4 nx = make_uint4(~0u, 0u, 0u, 0u);  // past the group's entries: a cell that none has
+    if (k + 4 < VALS) nx = *(const uint4*)(mine + k + 4);
+    const uint32_t en[5] = {e.x, e.y, e.z, e.w, nx.x};
+    float v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = park[(en[j] & 63u) * STRIDE + val];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t cell = en[j] >> 6;
+      sum += v[j];
+      if (cell != (en[j + 1] >> 6)) {
+        if (cell != FG_NONE && sum != 0.f) atomicAdd(base + (size_t)cell * VALS + val, sum);
+        sum = 0.f;
+      }
+    }
+    e = nx;
+  }
+}
+
+constexpr int FG_GS = FG_GREC + 4, FG_PS = FG_PREC + 4;  // parked row strides: 16-byte rows, spread over the banks
+
+struct FieldGradLds {
+  float park[64 * FG_GS];  // grid records, then each plane's (64 * FG_PS)
+  uint32_t order[4][64];
+  uint32_t queue[128];     // nodes with a segment, waiting for a full wave
+};
+
+// One wave's 64 (or at the end fewer) exterior segments, all samples
+__device__ __forceinline__ void field_grad_wave(const FieldDev& F, const Gen& q, bool act, uint32_t i,
+                                                const float4* fseg, FieldGradLds& lds, float* gdst, float* pdst) {
   const int lane = (int)(threadIdx.x & 63u);
-  park[lane][48] = __int_as_float(key);
-  wave_lds_sync();
-  uint64_t pending = __ballot(key >= 0);
-  while (pending) {
-    const int leader = __ffsll((unsigned long long)pending) - 1;
-    const int kl = __builtin_amdgcn_readlane(key, leader);
-    const uint64_t m = __ballot(key == kl);
-    pending &= ~m;
-    if (lane < FG_GREC) {
-      float sum = 0.f;
-      for (uint64_t mm = m; mm; mm &= mm - 1ull) sum += park[__ffsll((unsigned long long)mm) - 1][lane];
-      if (sum != 0.f) atomicAdd(base + (size_t)kl * FG_GREC + lane, sum);
-    }
+  const int cx = F.nx - 1, cy = F.ny - 1, pc = F.res - 1;
+  const int S = F.samples;
+  bool open = false;
+  v3 o = mk3(0.f, 0.f, 0.f), d = o, Lt = o, Lb = o;
+  float tend = 0.f;
+  if (act) {
+    const float4 b = fseg[2 * (size_t)i + 1], a = fseg[2 * (size_t)i];
+    open = b.w > 1.5f;
+    Lt = xyz(a);
+    tend = open ? 0.f : a.w;
+    Lb = xyz(b);
+    o = xyz(q.o[i]);
+    d = xyz(q.d[i]);
   }
-  wave_lds_sync();
+  FieldClip cl;
+  cl.s0 = cl.s1 = 0.f;
+  if (act && !field_clip(F, o, d, tend, open, cl)) act = false;
+  const float h = act ? (cl.s1 - cl.s0) / (float)S : 0.f;
+  v3 P = mk3(0.f, 0.f, 0.f);
+  float Tk = 1.f;
+  float* row = lds.park + lane * FG_GS;
+  float* prow = lds.park + lane * FG_PS;
+  for (int k = 0; k < S; ++k) {
+    float fb[4] = {0.f, 0.f, 0.f, 0.f};
+    v3 xk = mk3(0.f, 0.f, 0.f);
+    if (act) {
+      xk = o + d * (cl.s0 + h * ((float)k + 0.5f));
+      float f[4];
+      field_feature(F, xk, f);
+      const float sig = softplusf(f[0]);
+      const float a = expf(-sig * h);
+      const v3 c = mk3(f[1], f[2], f[3]);
+      const float w = Tk * (1.f - a);
+      P = P + c * w;
+      const float Tn = Tk * a;
+      const v3 after = Lt - P;
+      const float gg = dot(Lb, c * Tn - after);
+      fb[0] = h * gg / (1.f + expf(-f[0]));
+      fb[1] = w * Lb.x;
+      fb[2] = w * Lb.y;
+      fb[3] = w * Lb.z;
+      Tk = Tn;
+    }
+    const float xs[3] = {xk.x, xk.y, xk.z};
+    FieldAxis ga[3], pa[3];
+    const int nn[3] = {F.nx, F.ny, F.nz};
+#pragma unroll
+    for (int ax = 0; ax < 3; ++ax) {
+      ga[ax] = field_axis(xs[ax], F.lo[ax], F.sg[ax], nn[ax]);
+      pa[ax] = field_axis(xs[ax], F.lo[ax], F.sp[ax], F.res);
+    }
+    const uint32_t none = (FG_NONE << 6) | (uint32_t)lane;
+    lds.order[0][lane] =
+        sort64(act ? ((uint32_t)((ga[2].i * cy + ga[1].i) * cx + ga[0].i) << 6) | (uint32_t)lane : none, lane);
+#pragma unroll
+    for (int qp = 0; qp < 3; ++qp) {
+      const int a = qp == 2 ? 1 : 0, b = qp == 0 ? 1 : 2;
+      lds.order[1 + qp][lane] =
+          sort64(act ? ((uint32_t)((qp * pc + pa[b].i) * pc + pa[a].i) << 6) | (uint32_t)lane : none, lane);
+    }
+    // the grid cell's record: corner c = (dx, dy, dz) bits 0-2, channel ch
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const float wx = (c & 1) ? ga[0].f : 1.f - ga[0].f, wy = ((c >> 1) & 1) ? ga[1].f : 1.f - ga[1].f;
+      const float wz = (c >> 2) ? ga[2].f : 1.f - ga[2].f;
+      const float wc = wx * wy * wz;
+      *(float4*)(row + 4 * c) = make_float4(wc * fb[0], wc * fb[1], wc * fb[2], wc * fb[3]);
+    }
+    wave_lds_sync();
+    add_sorted<FG_GREC, FG_GS>(lds.park, lds.order[0], gdst);
+    // each plane's cell: (x, y), (x, z), (y, z); corner (di, dj), channel ch
+#pragma unroll
+    for (int qp = 0; qp < 3; ++qp) {
+      const int a = qp == 2 ? 1 : 0, b = qp == 0 ? 1 : 2;
+      wave_lds_sync();
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const float wa = (c & 1) ? pa[a].f : 1.f - pa[a].f, wb = (c >> 1) ? pa[b].f : 1.f - pa[b].f;
+        const float wc = wa * wb;
+        *(float4*)(prow + 4 * c) = make_float4(wc * fb[0], wc * fb[1], wc * fb[2], wc * fb[3]);
+      }
+      wave_lds_sync();
+      add_sorted<FG_PREC, FG_PS>(lds.park, lds.order[1 + qp], pdst);
+    }
+    wave_lds_sync();
+  }
 }
 
-// the same for the three planes' records at once (plane q's FG_PREC values
-// parked at 16 q, its key k[q]): lanes 16 q .. 16 q + 15 take plane q's
-// distinct cells, so a pass adds up to one cell of each plane
-__device__ __forceinline__ void merge_planes(float (*park)[FG_PARK], const int k[3], float* base) {
-  const int lane = (int)(threadIdx.x & 63u), grp = lane >> 4, comp = lane & 15;
-  uint64_t pend0 = __ballot(k[0] >= 0), pend1 = __ballot(k[1] >= 0), pend2 = __ballot(k[2] >= 0);
-  wave_lds_sync();
-  while (pend0 | pend1 | pend2) {
-    int k0 = -1, k1 = -1, k2 = -1;
-    uint64_t m0 = 0ull, m1 = 0ull, m2 = 0ull;
-    if (pend0) {
-      k0 = __builtin_amdgcn_readlane(k[0], __ffsll((unsigned long long)pend0) - 1);
-      m0 = __ballot(k[0] == k0);
-      pend0 &= ~m0;
-    }
-    if (pend1) {
-      k1 = __builtin_amdgcn_readlane(k[1], __ffsll((unsigned long long)pend1) - 1);
-      m1 = __ballot(k[1] == k1);
-      pend1 &= ~m1;
-    }
-    if (pend2) {
-      k2 = __builtin_amdgcn_readlane(k[2], __ffsll((unsigned long long)pend2) - 1);
-      m2 = __ballot(k[2] == k2);
-      pend2 &= ~m2;
-    }
-    const int kg = grp == 0 ? k0 : (grp == 1 ? k1 : (grp == 2 ? k2 : -1));
-    if (kg >= 0) {
-      float sum = 0.f;
-      for (uint64_t mm = grp == 0 ? m0 : (grp == 1 ? m1 : m2); mm; mm &= mm - 1ull)
-        sum += park[__ffsll((unsigned long long)mm) - 1][16 * grp + comp];
-      if (sum != 0.f) atomicAdd(base + (size_t)kg * FG_PREC + comp, sum);
-    }
-  }
-  wave_lds_sync();
-}
-
+// Past the camera rays about half a generation's nodes have an exterior segment
+// (the others lie inside the object), so a wave collects them and works on 64 at
+// a time.
 __global__ void __launch_bounds__(FG_T) k_field_grad(FieldDev F, Gen q, int g, const Counters* ctr,
                                                      const float4* fseg, float* copies, int n_copies) {
-  __shared__ float park[FG_T / 64][64][FG_PARK];
+  __shared__ __align__(16) FieldGradLds sh[FG_T / 64];
+  FieldGradLds& lds = sh[threadIdx.x >> 6];
   const int64_t n = ctr->count[g];
-  const int lane = (int)(threadIdx.x & 63u), wv = (int)(threadIdx.x >> 6);
-  const int cx = F.nx - 1, cy = F.ny - 1, pc = F.res - 1;
+  const int lane = (int)(threadIdx.x & 63u);
   float* gdst = copies + (size_t)(blockIdx.x % (unsigned)n_copies) * field_rec_floats(F);
-  float* pdst = gdst + (size_t)FG_GREC * cx * cy * (F.nz - 1);
-  const int S = F.samples;
-  for (int64_t base = (int64_t)blockIdx.x * FG_T; base < n; base += (int64_t)gridDim.x * FG_T) {
-    const int64_t i = base + threadIdx.x;
-    bool act = false, open = false;
-    v3 o = mk3(0.f, 0.f, 0.f), d = o, Lt = o, Lb = o;
-    float tend = 0.f;
-    if (i < n) {
-      const float4 b = fseg[2 * i + 1];
-      if (b.w != 0.f) {
-        const float4 a = fseg[2 * i];
-        act = true;
-        open = b.w > 1.5f;
-        Lt = xyz(a);
-        tend = a.w;
-        Lb = xyz(b);
-        o = xyz(q.o[i]);
-        d = xyz(q.d[i]);
-      }
-    }
-    FieldClip cl;
-    cl.s0 = cl.s1 = 0.f;
-    if (act && !field_clip(F, o, d, tend, open, cl)) act = false;
-    const float h = act ? (cl.s1 - cl.s0) / (float)S : 0.f;
-    v3 P = mk3(0.f, 0.f, 0.f);
-    float Tk = 1.f;
-    for (int k = 0; k < S; ++k) {
-      float fb[4] = {0.f, 0.f, 0.f, 0.f};
-      v3 xk = mk3(0.f, 0.f, 0.f);
-      if (act) {
-        xk = o + d * (cl.s0 + h * ((float)k + 0.5f));
-        float f[4];
-        field_feature(F, xk, f);
-        const float sig = softplusf(f[0]);
-        const float a = expf(-sig * h);
-        const v3 c = mk3(f[1], f[2], f[3]);
-        const float w = Tk * (1.f - a);
-        P = P + c * w;
-        const float Tn = Tk * a;
-        const v3 after = Lt - P;
-        const float gg = dot(Lb, c * Tn - after);
-        fb[0] = h * gg / (1.f + expf(-f[0]));
-        fb[1] = w * Lb.x;
-        fb[2] = w * Lb.y;
-        fb[3] = w * Lb.z;
-        Tk = Tn;
-      }
-      const float xs[3] = {xk.x, xk.y, xk.z};
-      FieldAxis ga[3], pa[3];
-      const int nn[3] = {F.nx, F.ny, F.nz};
-#pragma unroll
-      for (int ax = 0; ax < 3; ++ax) {
-        ga[ax] = field_axis(xs[ax], F.lo[ax], F.sg[ax], nn[ax]);
-        pa[ax] = field_axis(xs[ax], F.lo[ax], F.sp[ax], F.res);
-      }
-      // the grid cell's record: corner c = (dx, dy, dz) bits 0-2, channel ch
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const float wx = (c & 1) ? ga[0].f : 1.f - ga[0].f, wy = ((c >> 1) & 1) ? ga[1].f : 1.f - ga[1].f;
-        const float wz = (c >> 2) ? ga[2].f : 1.f - ga[2].f;
-        const float wc = wx * wy * wz;
-#pragma unroll
-        for (int ch = 0; ch < 4; ++ch) park[wv][lane][4 * c + ch] = wc * fb[ch];
-      }
-      merge_grid(park[wv], act ? (ga[2].i * cy + ga[1].i) * cx + ga[0].i : -1, gdst);
-      // each plane's cell: (x, y), (x, z), (y, z); corner (di, dj), channel ch
-      int kp[3];
-#pragma unroll
-      for (int qp = 0; qp < 3; ++qp) {
-        const int a = qp == 2 ? 1 : 0, b = qp == 0 ? 1 : 2;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const float wa = (c & 1) ? pa[a].f : 1.f - pa[a].f, wb = (c >> 1) ? pa[b].f : 1.f - pa[b].f;
-#pragma unroll
-          for (int ch = 0; ch < 4; ++ch) park[wv][lane][16 * qp + 4 * c + ch] = wa * wb * fb[ch];
-        }
-        kp[qp] = act ? (qp * pc + pa[b].i) * pc + pa[a].i : -1;
-      }
-      merge_planes(park[wv], kp, pdst);
-    }
+  float* pdst = gdst + (size_t)FG_GREC * (F.nx - 1) * (F.ny - 1) * (F.nz - 1);
+  const int64_t waves = (int64_t)gridDim.x * (FG_T / 64);
+  int queued = 0;  // wave-uniform
+  for (int64_t base = ((int64_t)blockIdx.x * (FG_T / 64) + (threadIdx.x >> 6)) * 64; base < n; base += waves * 64) {
+    const int64_t i = base + lane;
+    const bool has = i < n && fseg[2 * i + 1].w != 0.f;
+    const uint64_t m = __ballot(has);
+    if (has) lds.queue[queued + __popcll(m & ((1ull << lane) - 1ull))] = (uint32_t)i;
+    queued += __popcll(m);
+    if (queued < 64) continue;
+    queued -= 64;
+    wave_lds_sync();
+    field_grad_wave(F, q, true, lds.queue[queued + lane], fseg, lds, gdst, pdst);
+    wave_lds_sync();
   }
+  wave_lds_sync();
+  if (queued > 0) field_grad_wave(F, q, lane < queued, lane < queued ? lds.queue[lane] : 0u, fseg, lds, gdst, pdst);
 }
 
 // d_grid and d_planes from the cell records: a node is corner (dx, dy, dz) of
@@ -2080,16 +2171,18 @@ extern "C" dt_status dt_trace_backward(const dt_scene* scene, const dt_rays* ray
 #define DT_ADJ(G, FL)                                                                                  \
   hipLaunchKernelGGL((k_adjoint<G, FL>), dim3((unsigned)blocks), dim3(AB), 0, s, sc, q, g, ctr, grad_rgb,  \
                      adj[(g + 1) & 1], adj[g & 1], frec, fkey, fcnt, red, fseg)
-    if (sc.fd.grid) {
-      if (sc.ab.mu) DT_ADJ(true, true); else DT_ADJ(false, true);
+    if (sc.fd.grid && sc.fd.d_grid && !fseg) {
+      if (sc.ab.mu) DT_ADJ(true, 2); else DT_ADJ(false, 2);
+    } else if (sc.fd.grid) {
+      if (sc.ab.mu) DT_ADJ(true, 1); else DT_ADJ(false, 1);
     } else {
-      if (sc.ab.mu) DT_ADJ(true, false); else DT_ADJ(false, false);
+      if (sc.ab.mu) DT_ADJ(true, 0); else DT_ADJ(false, 0);
     }
 #undef DT_ADJ
     if (sc.env.d_tex) {
       const int64_t eb = (P.cap[g] + GG_T - 1) / GG_T;
       hipLaunchKernelGGL(k_env_tex_grad, dim3((unsigned)(eb < 8192 ? eb : 8192)), dim3(GG_T), 0, s, sc, q, g,
-                         ctr, grad_rgb);
+                         ctr, grad_rgb, fseg);
     }
     if (fseg) {
       const int64_t fb = (P.cap[g] + FG_T - 1) / FG_T;
