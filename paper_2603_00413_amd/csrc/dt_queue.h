@@ -4,6 +4,10 @@
 #include "dt_device.h"
 
 constexpr uint32_t RAY_INSIDE = 1u;  // ray flag: travelling inside the object
+// on the tape of a checkpointed trace, a stored ray's flags also hold its hit
+// triangle + 1 from this bit up (0: a miss)
+constexpr int RAY_TRI_SHIFT = 4;
+static_assert(((uint64_t)DT_MAX_FACES << RAY_TRI_SHIFT) < (1ull << 32), "triangle ids fit beside the flags");
 
 // 64-bit mixer: the SplitMix64 output function (Steele, Lea and Flood,
 // OOPSLA 2014).  Summed over a pixel's segments it gives an order-independent
@@ -209,12 +213,19 @@ dt_status mlp_trace_backward(const EnvDev& e, Gen q, const uint32_t* list, const
                              int g, int64_t cap, const float* grad_rgb, Adj cur, hipStream_t s);
 // the same adjoint, also adding each block's share of dLoss/d(weights, biases)
 // into its row of part (rows of mlp_wgrad_params(e) floats, zeroed by the
-// caller before the first generation); 64-wide networks
+// caller before the first generation); 64-wide networks.  The rows are two runs
+// of MLP_WG_ROWS: the second lies where a field's gradient would (a field and a
+// network do not go together), so the workspace holds one.
+constexpr int MLP_WG_ROWS = 256;
+struct MlpParts {
+  float* run[2];
+};
 dt_status mlp_trace_backward_wgrad(const EnvDev& e, Gen q, const uint32_t* list, const Counters* ctr,
-                                   int g, const float* grad_rgb, Adj cur, float* part, hipStream_t s);
+                                   int g, const float* grad_rgb, Adj cur, MlpParts part, hipStream_t s);
 // e.d_w / e.d_b = the rows of part summed in order
-dt_status mlp_wgrad_reduce(const EnvDev& e, const float* part, hipStream_t s);
+dt_status mlp_wgrad_reduce(const EnvDev& e, MlpParts part, hipStream_t s);
 // parameters of a network (0 when the weight gradient is not supported), and
-// the scratch bytes the partial sums of the largest supported one need
+// the scratch bytes a run of partial sums of the largest supported one needs
 int64_t mlp_wgrad_params(const EnvDev& e);
-size_t mlp_wgrad_scratch_bytes();
+constexpr size_t MLP_WG_BYTES = sizeof(float) * MLP_WG_ROWS * (4096 * 4 + 192 + 64 * 4 + 3);
+inline size_t mlp_wgrad_scratch_bytes() { return MLP_WG_BYTES; }

@@ -294,8 +294,8 @@ __device__ __forceinline__ uint4 wfrag_t(const uint16_t* w, int ib, int kc, int 
 // 581 us with the whole gradient in each wave's accumulators, no barriers and one
 // wave per SIMD; 365 us this way.)
 constexpr int WG_T = 256;
-constexpr int WG_RAYS = WG_T / 4;  // rays of a round
-constexpr int WG_BLOCKS = 512;     // blocks of the weight-gradient backward (rows of partials)
+constexpr int WG_RAYS = WG_T / 4;           // rays of a round
+constexpr int WG_BLOCKS = 2 * MLP_WG_ROWS;  // blocks of the weight-gradient backward (rows of partials)
 constexpr int WG_LD = 64 + 4;      // a write takes 7.2 cycles of the LDS, a transposing read 4.3, without conflicts
 constexpr int WG_PART = WG_RAYS * WG_LD;  // one staged part: [ray][feature]
 
@@ -689,7 +689,7 @@ __global__ void __launch_bounds__(MLP_T) k_mlp_trace_bwd(EnvDev e, Gen q, const 
 template <int NL>
 __global__ void __launch_bounds__(WG_T, 2) k_mlp_trace_bwd_wg(EnvDev e, Gen q, const uint32_t* list,
                                                               const Counters* ctr, int g, const float* grad_rgb,
-                                                              Adj cur, float* part) {
+                                                              Adj cur, MlpParts part) {
   using N = NetLds<64, NL>;
   using W = Wg<NL>;
   __shared__ __align__(16) unsigned char net[N::BYTES];
@@ -720,7 +720,7 @@ __global__ void __launch_bounds__(WG_T, 2) k_mlp_trace_bwd_wg(EnvDev e, Gen q, c
         mlp_wave<64, NL, true, true>(per_group(sw), sb, e.n_freq, xyz(r.d), [&] { return gb; }, &db, stage, &wg);
     miss_store(cur, r, E, db);
   });
-  float* row = part + (size_t)blockIdx.x * W::n_params;
+  float* row = part.run[blockIdx.x / MLP_WG_ROWS] + (size_t)(blockIdx.x % MLP_WG_ROWS) * W::n_params;
 #pragma unroll
   for (int L = 0; L < NL; ++L) {
 #pragma unroll
@@ -734,12 +734,13 @@ __global__ void __launch_bounds__(WG_T, 2) k_mlp_trace_bwd_wg(EnvDev e, Gen q, c
 
 // d_w[k] (k < n_weights) and d_b[k - n_weights]: the blocks' partial sums,
 // added in block order
-__global__ void k_mlp_wg_reduce(const float* part, int64_t n_params, int64_t n_weights, float* d_w,
+__global__ void k_mlp_wg_reduce(MlpParts part, int64_t n_params, int64_t n_weights, float* d_w,
                                 float* d_b) {
   for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n_params;
        k += (int64_t)gridDim.x * blockDim.x) {
     double s = 0.0;
-    for (int b = 0; b < WG_BLOCKS; ++b) s += (double)part[(size_t)b * n_params + k];
+    for (int r = 0; r < 2; ++r)
+      for (int b = 0; b < MLP_WG_ROWS; ++b) s += (double)part.run[r][(size_t)b * n_params + k];
     if (k < n_weights)
       d_w[k] = (float)s;
     else
@@ -803,11 +804,9 @@ int64_t mlp_wgrad_params(const EnvDev& e) {
   return e.hidden == 64 ? 4096 * (int64_t)e.n_layers + 192 + 64 * (int64_t)e.n_layers + 3 : 0;
 }
 
-size_t mlp_wgrad_scratch_bytes() {
-  return sizeof(float) * (size_t)WG_BLOCKS * (size_t)Wg<4>::n_params;
-}
+static_assert(MLP_WG_BYTES >= sizeof(float) * MLP_WG_ROWS * Wg<4>::n_params, "run of partial sums");
 
-dt_status mlp_wgrad_reduce(const EnvDev& e, const float* part, hipStream_t s) {
+dt_status mlp_wgrad_reduce(const EnvDev& e, MlpParts part, hipStream_t s) {
   const int64_t np = mlp_wgrad_params(e);
   const int64_t nw = np - 64 * (int64_t)e.n_layers - 3;
   hipLaunchKernelGGL(k_mlp_wg_reduce, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, s, part, np, nw,
@@ -817,7 +816,7 @@ dt_status mlp_wgrad_reduce(const EnvDev& e, const float* part, hipStream_t s) {
 }
 
 dt_status mlp_trace_backward_wgrad(const EnvDev& e, Gen q, const uint32_t* list, const Counters* ctr,
-                                   int g, const float* grad_rgb, Adj cur, float* part, hipStream_t s) {
+                                   int g, const float* grad_rgb, Adj cur, MlpParts part, hipStream_t s) {
 #define X(L)                                                                                    \
   if (e.hidden == 64 && e.n_layers == L) {                                                      \
     hipLaunchKernelGGL(k_mlp_trace_bwd_wg<L>, dim3(WG_BLOCKS), dim3(WG_T), 0, s, e, q, \
