@@ -403,6 +403,82 @@ __device__ __forceinline__ void trav_visit(Trav& s, const BvhView& bv, uint2* st
   }
 }
 
+// The same step for a ray that eight lanes share (all holding its state): lane c
+// of the eight tests child c's box, with the operations of trav_visit, and the
+// wave's ballot gives each group its mask.  lm: this lane's child is a leaf that
+// the ray enters; its leaf index is lbase plus the number of bits of lall below c.
+// stk: the group's column of the whole stack (DT_STACK entries).
+__device__ __forceinline__ void trav_visit_shared(Trav& s, const BvhView& bv, uint2* stk, int stride, bool& lm,
+                                                  uint32_t& lall, uint32_t& lbase) {
+  const int lane = (int)(threadIdx.x & 63u), c = lane & 7;
+  bool enters = false;
+  uint4 A = make_uint4(0u, 0u, 0u, 0u);
+  uint32_t eb = 0;
+  const bool go = !s.done && s.node < (uint32_t)wide_cap(bv.nf);
+  if (go) {
+    const WideNode& n = bv.wide[s.node];
+    const float4 org = n.org;
+    A = n.a;
+    const uint4 B = n.b, C = n.c;
+    eb = __float_as_uint(org.w);
+    const float ax = ldexpf(s.r.inv.x, (int)(int8_t)(eb & 0xFFu));
+    const float ay = ldexpf(s.r.inv.y, (int)(int8_t)((eb >> 8) & 0xFFu));
+    const float az = ldexpf(s.r.inv.z, (int)(int8_t)((eb >> 16) & 0xFFu));
+    const float ox = org.x - s.r.o.x, oy = org.y - s.r.o.y, oz = org.z - s.r.o.z;
+    const bool hi = c >= 4, px = !(s.r.inv.x < 0.f), py = !(s.r.inv.y < 0.f), pz = !(s.r.inv.z < 0.f);
+    const int sh = 8 * (c & 3);
+    auto near_far = [&](bool pos, uint32_t lo, uint32_t up, uint32_t two, uint32_t& nq, uint32_t& fq) {
+      const uint32_t l = hi ? two : lo, u = hi ? two >> 16 : up;
+      nq = ((pos ? l : u) >> sh) & 0xFFu;
+      fq = ((pos ? u : l) >> sh) & 0xFFu;
+    };
+    uint32_t nx, fx, ny, fy, nz, fz;
+    near_far(px, A.z, A.w, C.x, nx, fx);
+    near_far(py, B.x, B.y, C.y, ny, fy);
+    near_far(pz, B.z, B.w, C.z, nz, fz);
+    const float tnx = fmaf((float)nx, ax, fmaf(ox, s.r.inv.x, -s.slack.x));
+    const float tny = fmaf((float)ny, ay, fmaf(oy, s.r.inv.y, -s.slack.y));
+    const float tnz = fmaf((float)nz, az, fmaf(oz, s.r.inv.z, -s.slack.z));
+    const float tfx = fmaf((float)fx, ax, fmaf(ox, s.r.inv.x, s.slack.x));
+    const float tfy = fmaf((float)fy, ay, fmaf(oy, s.r.inv.y, s.slack.y));
+    const float tfz = fmaf((float)fz, az, fmaf(oz, s.r.inv.z, s.slack.z));
+    const float tn = fmaxf(fmaxf(tnx, tny), fmaxf(tnz, 0.0f));
+    const float tf = fminf(fminf(tfx, tfy), fminf(tfz, s.h.t * 1.0000008f));
+    enters = c < DT_WIDE && tn <= tf;
+  }
+  const uint32_t hit = (uint32_t)(__ballot(enters) >> (lane & 56)) & 0x3Fu;
+  lm = false;
+  if (s.done) return;
+  if (!go) {
+    s.overflow = true;
+    s.done = true;
+    return;
+  }
+  const uint32_t im = (eb >> 24) & 0x3Fu;
+  lall = A.x >> 26;
+  lbase = A.y;
+  lm = c < DT_WIDE && ((hit & lall) >> c) & 1u;
+  const uint32_t ih = hit & im;
+  uint2 g = make_uint2((A.x & DT_WIDE_INDEX) | (ih << 26), im | (((s.neg >> (eb >> 30)) & 1u) << 8));
+  if (ih == 0u) {
+    if (s.sp == 0) {
+      s.done = true;
+      return;
+    }
+    g = stk[--s.sp * stride];
+  }
+  const uint32_t m = g.x >> 26;
+  const uint32_t bit = (g.y & 256u) ? 0x80000000u >> __clz((int)m) : m & (0u - m);
+  s.node = (g.x & DT_WIDE_INDEX) + (uint32_t)__popc(g.y & 0x3Fu & (bit - 1u));
+  if (m != bit) {
+    g.x &= ~(bit << 26);
+    if (s.sp < DT_STACK)
+      stk[s.sp++ * stride] = g;
+    else
+      s.overflow = true;
+  }
+}
+
 // Closest hits of a wave's 64 rays, leaf tests batched across the wave.
 //
 // A lane's ray visits nodes as in trav_visit, but the leaf children it enters
@@ -423,7 +499,10 @@ __device__ __forceinline__ void trav_visit(Trav& s, const BvhView& bv, uint2* st
 // without a ray).  SCENE_PER_LANE: lanes may trace different scenes (the
 // owner's leaf array and t_eps travel with the candidate).  ANY: a lane stops
 // at its first hit, whichever it is (tri >= 0, t one of its hits'), and
-// triangle skip2 is ignored as well.
+// triangle skip2 is ignored as well.  SHARED: the wave has 8 rays, eight
+// consecutive lanes each (same arguments in all eight, and the same result);
+// leaves are tested once SHARED_ROUND of them wait, as few rays fill a round of
+// 64 only when the traversal is over, and until then prune nothing.
 #define DT_LQ_CAP 128
 struct LeafQueue {
   uint32_t req[DT_LQ_CAP];       // (leaf << 6) | owner lane
@@ -436,12 +515,14 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-template <int SL, bool GLOBAL, bool SCENE_PER_LANE, bool ANY = false>
+constexpr uint32_t SHARED_ROUND = 16;
+template <int SL, bool GLOBAL, bool SCENE_PER_LANE, bool ANY = false, bool SHARED = false>
 __device__ __forceinline__ Hit closest_hit_wave(const BvhView& bv, bool active, v3 o, v3 d,
                                                 int skip, float t_eps, uint2* stk, int stride,
                                                 uint2* gstk, int gcap, LeafQueue& lq,
                                                 bool* overflow, int skip2 = -1) {
   const int lane = (int)(threadIdx.x & 63u);
+  const int own = SHARED ? lane & 56 : lane;  // the ray's place among the owners
   const uint64_t lt = (1ull << lane) - 1ull;
   Trav s;
   trav_init(s, bv, o, d, skip, t_eps);
@@ -498,7 +579,7 @@ __device__ __forceinline__ Hit closest_hit_wave(const BvhView& bv, bool active, 
       }
     }
     wave_lds_sync();
-    const unsigned long long kb = lq.best[lane];
+    const unsigned long long kb = lq.best[own];
     if (kb != ~0ull) {
       s.h.t = __uint_as_float((uint32_t)(kb >> 32));
       s.h.tri = (int)(uint32_t)kb;
@@ -512,6 +593,22 @@ __device__ __forceinline__ Hit closest_hit_wave(const BvhView& bv, bool active, 
   const uint32_t most = (uint32_t)wide_cap(bv.nf) + 64u;
   for (uint32_t step = 0; __ballot(!s.done) != 0ull; ++step) {
     uint32_t lm = 0u, lall = 0u, lbase = 0u;
+    if constexpr (SHARED) {
+      bool mine = false;
+      if (!s.done && step > most) {
+        s.overflow = true;
+        s.done = true;
+      }
+      trav_visit_shared(s, bv, stk, stride, mine, lall, lbase);
+      const uint64_t b = __ballot(mine);
+      if (mine) {
+        const uint32_t leaf = min(lbase + (uint32_t)__popc(lall & ((1u << (lane & 7)) - 1u)), (uint32_t)(bv.nf - 1));
+        lq.req[qn + (uint32_t)__popcll(b & lt)] = (leaf << 6) | (uint32_t)own;
+      }
+      qn += (uint32_t)__popcll(b);  // at most SHARED_ROUND - 1 + 48
+      if (qn >= SHARED_ROUND) rounds(1u);
+      continue;
+    }
     if (!s.done) {
       if (step > most) {
         s.overflow = true;
@@ -538,7 +635,7 @@ __device__ __forceinline__ Hit closest_hit_wave(const BvhView& bv, bool active, 
   Hit h = s.h;
   if (!ANY && queued) {
     const float4* L = bv.leaves;
-    const uint32_t j = lq.win[lane];
+    const uint32_t j = lq.win[own];
     const float4 p0 = L[3 * j];
     Hit r;
     r.tri = -1;

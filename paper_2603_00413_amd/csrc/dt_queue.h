@@ -68,7 +68,8 @@ __device__ __forceinline__ bool claim_batch(WorkPart* wp, uint32_t nb, uint32_t 
 // the longest chain of node visits in a wave, and by the 64 separate lines a
 // wave's node fetch asks for, so its batches shrink, to no less than 8 rays,
 // until there are DT_WAVES_WANTED of them (one per SIMD): measured per launch,
-// 5,000 rays on 102,400 faces 81 -> 75 us, 4,096 rays on 1,280 faces 32 -> 25 us.
+// 5,000 rays on 102,400 faces 81 -> 75 us, 4,096 rays on 1,280 faces 32 -> 25 us
+// (59 and 23 us with the lanes of such a wave shared among its rays, k_trace).
 constexpr uint32_t DT_WAVES_WANTED = 1024;
 constexpr uint32_t DT_MIN_BATCH = 8;
 __device__ __forceinline__ uint32_t batch_rays(uint32_t n) {

@@ -290,17 +290,31 @@ __device__ __forceinline__ v3 mul3(v3 a, v3 b) { return mk3(a.x * b.x, a.y * b.y
 
 
 // ------------------------------------------------------------------ k_trace (a4 + a5 decisions + a6)
-template <bool GRID, bool FIELD>
+// SHORT: a queue of at most SHARED_RAYS rays is traced with eight lanes to a ray,
+// a box each: such a queue leaves SIMDs empty, and is bound by the chain of
+// instructions and fetches from visit to visit, which loses its 6-fold box tests
+// and whose leaves are tested soon enough to prune.  Measured with one lane to a
+// ray and shared: 5,000 rays on 102,400 faces 73 -> 59 us a generation, a training
+// batch of 20,000 on as many 1,142 -> 1,053 us, of 30,000 1,180 -> 1,110 (sharing
+// stopped at 16,384: 1,149 and 1,189), a view of 160 x 120 558 -> 484.  Both
+// traversals together spill 44 bytes at the seven waves a SIMD that long queues
+// want, so the kernel that holds both is launched for queues of a capacity of at
+// most SHORT_CAP only (2^18 to 2^20: no gain, a view of 400 x 300 647 -> 652 us).
+constexpr uint32_t SHARED_RAYS = 32768;
+constexpr int64_t SHORT_CAP = 1 << 17;
+template <bool GRID, bool FIELD, bool SHORT>
 __global__ void __launch_bounds__(TB, FIELD ? 4 : 7) k_trace(SceneDev sc, Gen q, int g, Counters* ctr,
                                               unsigned long long* part, float* rgb, float* wtrunc,
                                               int32_t* flags, unsigned long long* sig,
                                               int accumulate, int note, uint2* ovf, WorkPart* wp, float4* att) {
-  __shared__ uint2 stk[DT_STACK_LDS * TB];
+  __shared__ uint2 stk[DT_STACK_LDS * TB];  // or 8 columns of DT_STACK entries
+  static_assert(DT_STACK_LDS * TB >= 8 * DT_STACK, "whole stacks of eight rays");
   __shared__ LeafQueue lq;
   uint2* gstk = ovf + (size_t)(blockIdx.x * TB + threadIdx.x) * (DT_STACK - DT_STACK_LDS);
   const uint32_t n = ctr->count[g];
   const int lane = threadIdx.x & 63;
-  const uint32_t rays = batch_rays(n), nb = (n + rays - 1u) / rays;
+  const bool shared = SHORT && n <= SHARED_RAYS;
+  const uint32_t rays = shared ? 8u : batch_rays(n), nb = (n + rays - 1u) / rays;
   const uint32_t x0 = blockIdx.x % (unsigned)DT_WORK_PARTS;
   uint32_t p = x0, batch = 0;
   bool first = true;
@@ -311,15 +325,31 @@ __global__ void __launch_bounds__(TB, FIELD ? 4 : 7) k_trace(SceneDev sc, Gen q,
     bool active = i < n && (uint32_t)lane < rays;
     bool has_r = false, has_t = false, hit = false;
     float4 o4 = make_float4(0.f, 0.f, 0.f, __int_as_float(-1)), d4 = make_float4(0.f, 0.f, 1.f, 0.f);
-    if (active) {
-      o4 = q.o[i];
-      d4 = q.d[i];
-    }
     bool ovf = false;
-    const Hit h = closest_hit_wave<DT_STACK_LDS, true, false>(sc.bvh, active, xyz(o4), xyz(d4),
-                                                              __float_as_int(o4.w), sc.t_eps,
-                                                              stk + threadIdx.x, TB, gstk,
-                                                              DT_STACK - DT_STACK_LDS, lq, &ovf);
+    Hit h;
+    if (SHORT && shared) {
+      const uint32_t k = base + (uint32_t)(lane >> 3);
+      const bool on = k < n;
+      if (on) {
+        o4 = q.o[k];
+        d4 = q.d[k];
+      }
+      h = closest_hit_wave<0, false, false, false, true>(sc.bvh, on, xyz(o4), xyz(d4), __float_as_int(o4.w), sc.t_eps,
+                                                         stk + (lane >> 3), 8, nullptr, 0, lq, &ovf);
+      const int src = (lane & 7) << 3;
+      h.t = __shfl(h.t, src);
+      h.tri = __shfl(h.tri, src);
+      h.b1 = __shfl(h.b1, src);
+      h.b2 = __shfl(h.b2, src);
+      ovf = __shfl((int)ovf, src) != 0;
+    } else {
+      if (active) {
+        o4 = q.o[i];
+        d4 = q.d[i];
+      }
+      h = closest_hit_wave<DT_STACK_LDS, true, false>(sc.bvh, active, xyz(o4), xyz(d4), __float_as_int(o4.w), sc.t_eps,
+                                                      stk + threadIdx.x, TB, gstk, DT_STACK - DT_STACK_LDS, lq, &ovf);
+    }
     if (active) {
       // reloaded rather than kept in registers through the traversal
       o4 = q.o[i];
@@ -1894,9 +1924,13 @@ dt_status run_generation(const SceneDev& sc, const Plan& P, int g, Gen cur, Gen 
                          uint32_t* miss_list, uint2* ovf, float4* att, hipStream_t s) {
   if (!sc.ab.mu && !sc.fd.grid) att = nullptr;  // the constant rate: recomputing it is cheaper
   if (dt_status st = record(events, 2 * g, s)) return st;
-#define DT_TRACE(G, FL)                                                                              \
-  hipLaunchKernelGGL((k_trace<G, FL>), dim3(trace_grid(P.cap[g])), dim3(TB), 0, s, sc, cur, g, ctr, part_g, \
+#define DT_TRACE_AS(G, FL, SH)                                                                                \
+  hipLaunchKernelGGL((k_trace<G, FL, SH>), dim3(trace_grid(P.cap[g])), dim3(TB), 0, s, sc, cur, g, ctr, part_g, \
                      rgb, wtrunc, flags, sig, accumulate, accumulate && noted, ovf, wp, att)
+#define DT_TRACE(G, FL)                                                                  \
+  do {                                                                                   \
+    if (P.cap[g] <= SHORT_CAP) DT_TRACE_AS(G, FL, true); else DT_TRACE_AS(G, FL, false); \
+  } while (0)
 #define DT_REPLAY(G, FL) \
   hipLaunchKernelGGL((k_replay<G, FL>), dim3(emit_grid(P.cap[g])), dim3(256), 0, s, sc, cur, g, ctr, part_g, att)
   if (noted && !accumulate) {
@@ -1911,6 +1945,7 @@ dt_status run_generation(const SceneDev& sc, const Plan& P, int g, Gen cur, Gen 
     if (sc.ab.mu) DT_TRACE(true, false); else DT_TRACE(false, false);
   }
 #undef DT_TRACE
+#undef DT_TRACE_AS
 #undef DT_REPLAY
   DT_CHECK_LAUNCH();
   if (dt_status st = record(events, 2 * g + 1, s)) return st;

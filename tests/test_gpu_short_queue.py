@@ -1,0 +1,55 @@
+"""Short queues are traced with eight lanes to a ray, longer ones with one: the
+same rays must take the same paths either way.  Their path signatures are
+compared exactly, their radiance to the order of a pixel's sum, for ray counts
+around a group, a wave and the longest short queue; one triangle included."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_00413_amd import binding as B
+from paper_2603_00413_amd import synth
+from tests.gpu_helpers import device
+
+pytestmark = pytest.mark.gpu
+LONG, DEPTH = 70000, 3
+
+
+def _trace(scene, o, d):
+    rays, p = B.Rays(o=o, d=d), B.Params(max_depth=DEPTH)
+    sig = torch.zeros(o.shape[0], dtype=torch.int64, device=o.device)
+    rgb = B.dt_trace_forward(scene, rays, p, B.Buffers(p, rays, scene.mesh, tape=False), path_sig=sig)[0]
+    return rgb, sig
+
+
+@pytest.fixture(scope="module", params=["torus", "triangle", "sliver"])
+def long_trace(request):
+    dev = device()
+    if request.param == "torus":
+        V, F = synth.displaced_torus(seed=6, nu=90, nv=41)
+    elif request.param == "triangle":
+        V, F = [[-1, -1, 0], [1, -1, 0.1], [0, 1, 0]], [[0, 1, 2]]
+    else:  # many faces in one place: deep stacks, equal boxes
+        k = np.arange(300)
+        V = np.stack([np.cos(k), np.sin(k), 1e-4 * k], 1)
+        F = np.stack([k, (k + 100) % 300, (k + 200) % 300], 1)
+    V, F = np.asarray(V, np.float32), np.asarray(F, np.int32)
+    mesh = B.Mesh(torch.from_numpy(V).to(dev), torch.from_numpy(F).to(dev))
+    env = B.Env(torch.from_numpy(synth.env_equirect(64, 32, seed=3)).to(dev))
+    scene = B.Scene(mesh, torch.tensor([1.4], device=dev), torch.tensor([0.3, 0.2, 0.1], device=dev), env)
+    rng = np.random.default_rng(8)
+    o = rng.normal(size=(LONG, 3))
+    o = 3.0 * o / np.linalg.norm(o, axis=1, keepdims=True)
+    d = rng.uniform(-0.9, 0.9, (LONG, 3)) - o
+    d[::7, 1:] = 0.0  # axis-aligned directions too
+    d /= np.linalg.norm(d, axis=1, keepdims=True)
+    o, d = (torch.from_numpy(x.astype(np.float32)).to(dev) for x in (o, d))
+    return scene, o, d, *_trace(scene, o, d)
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 63, 65, 513, 5000, 32768, 32769])
+def test_short_queue(long_trace, n):
+    scene, o, d, rgb, sig = long_trace
+    r, s = _trace(scene, o[:n].contiguous(), d[:n].contiguous())
+    assert torch.equal(s, sig[:n])
+    # a pixel sums at most 2^DEPTH paths, in any order
+    assert (r - rgb[:n]).abs().max() <= 2**DEPTH * 2**-23 * rgb.abs().max()
