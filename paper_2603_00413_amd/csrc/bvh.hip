@@ -31,12 +31,6 @@ __device__ T block_incl_scan(T v, T* sh) {
   return sh[t];
 }
 
-__global__ void k_fill_u32(uint32_t* p, uint32_t v, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-
 template <class T>
 __global__ void k_scan_reduce(const T* in, int32_t n, int32_t chunk, T* part) {
   __shared__ T sh[SCAN_T];
@@ -1112,18 +1106,7 @@ size_t carve_build(Carver& c, int32_t nv, int32_t nf, BuildWs* w) {
 
 }  // namespace
 
-// ------------------------------------------------------------------ shared helpers
-dt_status dt_fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t s) {
-  if (n <= 0) return DT_OK;
-  unsigned nb = dt_blocks(n, 256);
-  if (nb > 4096) nb = 4096;
-  hipLaunchKernelGGL(k_fill_u32, dim3(nb), dim3(256), 0, s, p, value, n);
-  DT_CHECK_LAUNCH();
-  return DT_OK;
-}
-
-size_t dt_scan_partials_count() { return SCAN_NB + 1; }
-
+// ------------------------------------------------------------------ scan
 // out[0..n) = exclusive prefix sums of in[0..n); partials[SCAN_NB] = total,
 // also to *total if given.  in == out is allowed.
 template <class T>
@@ -1140,11 +1123,6 @@ static dt_status scan_exclusive(const T* in, T* out, int32_t n, T* partials, T* 
   hipLaunchKernelGGL(k_scan_apply<T>, dim3(SCAN_NB), dim3(SCAN_T), 0, s, in, out, n, chunk, partials);
   DT_CHECK_LAUNCH();
   return DT_OK;
-}
-
-dt_status dt_scan_exclusive_i32(const int32_t* in, int32_t* out, int32_t n, int32_t* partials,
-                                hipStream_t s) {
-  return scan_exclusive(in, out, n, partials, (int32_t*)nullptr, s);
 }
 
 // stable LSD radix sort of (Morton key, face) in passes of 8 bits, then the

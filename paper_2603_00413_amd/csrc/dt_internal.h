@@ -208,8 +208,3 @@ inline unsigned dt_blocks(int64_t n, int threads) {
   return (unsigned)b;
 }
 
-// device-wide helpers (bvh.hip)
-dt_status dt_fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t s);
-dt_status dt_scan_exclusive_i32(const int32_t* in, int32_t* out, int32_t n, int32_t* partials,
-                                hipStream_t s);
-size_t dt_scan_partials_count();

@@ -147,8 +147,8 @@ dt_status chunk_scan(Counters* ctr, int g, unsigned long long* part, unsigned lo
 
 // Positions of the children of the rays [blk * EMIT_T, (blk + 1) * EMIT_T) of a
 // generation in the next queue, one ray per thread of a block: reflected
-// children fill [0, nrefl) in ray order, refracted ones follow.  part holds the
-// exclusive scan of the children per chunk of DT_CHUNK rays; what the chunk's
+// children fill [0, nrefl) in ray order, refracted ones follow.  base: the children
+// of the chunks (of DT_CHUNK rays) before this step's; what the chunk's
 // earlier rays emit is counted from their codes (at most 7 KB, read by the
 // whole block at once), so every block does one step of work: with a block
 // walking its chunk in eight dependent steps a short queue's few chunks took
@@ -160,7 +160,7 @@ struct EmitLds {
   uint32_t er[EMIT_T / 64], et[EMIT_T / 64];  // the chunk's earlier ones, as counted by each wave
 };
 
-__device__ __forceinline__ uint2 child_positions(const uint32_t* code, int64_t blk, const unsigned long long* part,
+__device__ __forceinline__ uint2 child_positions(const uint32_t* code, int64_t blk, unsigned long long base,
                                                  uint32_t nrefl, bool h_r, bool h_t, EmitLds& lds) {
   constexpr int PER = DT_CHUNK / EMIT_T;
   const int lane = (int)(threadIdx.x & 63u), wv = (int)(threadIdx.x >> 6);
@@ -182,7 +182,6 @@ __device__ __forceinline__ uint2 child_positions(const uint32_t* code, int64_t b
     lds.et[wv] = et;
   }
   __syncthreads();
-  const unsigned long long base = part[chunk];
   const uint64_t lt = (1ull << lane) - 1ull;
   uint32_t ir = (uint32_t)base + (uint32_t)__popcll(br & lt);
   uint32_t it = nrefl + (uint32_t)(base >> 32) + (uint32_t)__popcll(bt & lt);

@@ -319,7 +319,7 @@ __global__ void __launch_bounds__(EMIT_T) k_serve_emit(const ServeTables* T, Gen
     bool active = i < n;
     uint32_t code = active ? q.code[i] : 0u;
     bool hr = (code & C_HAS_R) != 0u, ht = (code & C_HAS_T) != 0u;
-    const uint2 at = child_positions(q.code, blk, part, nr_tot, hr, ht, lds);
+    const uint2 at = child_positions(q.code, blk, part[blk * EMIT_T / DT_CHUNK], nr_tot, hr, ht, lds);
     const uint32_t ir = at.x, it = at.y;
     if (active && (hr || ht)) {
       float4 o4 = q.o[i], d4 = q.d[i], w4 = q.w[i], h4 = q.hit[i];

@@ -55,7 +55,7 @@ struct Plan {
   size_t w_ro[2], w_rd[2], w_rw[2], w_hit, w_code;
   size_t w_adj[2][3];
   size_t w_dN, w_sbar, w_red, w_miss, w_ovf, w_gscr, w_mlpg, w_fscr, w_fseg;
-  size_t w_frec, w_fkey, w_fidx, w_fcnt, w_foff, w_fscan, w_fg;  // per-face gathering of vertex adjoints
+  size_t w_frec, w_fkey, w_fidx, w_fcnt, w_foff, w_fg;  // per-face gathering of vertex adjoints
   size_t w_seg_o, w_seg_d, w_seg_w, w_seg_hit, w_seg_code, w_seg_child;  // k generations each
   size_t ws_bytes;
 };
@@ -160,10 +160,8 @@ bool make_plan(const dt_trace_params* p, int64_t n_rays, int64_t npix, int32_t n
   o = dt_align(o + 4 * mc);
   P.w_fcnt = o;  // records per face
   o = dt_align(o + 4 * ((size_t)nf + 1));
-  P.w_foff = o;  // exclusive scan of the counts
+  P.w_foff = o;  // where each face's records go
   o = dt_align(o + 4 * ((size_t)nf + 1));
-  P.w_fscan = o;  // partial sums of the scan
-  o = dt_align(o + 4 * dt_scan_partials_count());
   P.w_fg = o;     // per-face running totals of the vertex adjoints
   o = dt_align(o + 4 * 18 * (size_t)nf);
   size_t kk = P.store_all ? 0 : (size_t)P.k;
@@ -184,65 +182,81 @@ bool make_plan(const dt_trace_params* p, int64_t n_rays, int64_t npix, int32_t n
 }
 
 // ------------------------------------------------------------------ small kernels
-__global__ void k_zero_f32(float* p, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 0.f;
-}
-__global__ void k_zero_u64(unsigned long long* p, int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 0ull;
-}
+// What a pass clears, in one launch with its counters (a launch each took 2 to 5
+// us, nine of them in a training step): ranges of 32-bit words, 16 bytes a store
+// between their unaligned ends.
+struct ClearList {
+  static constexpr int MAX = 14;
+  uint32_t* p[MAX];
+  int64_t n[MAX];  // words
+  int k = 0;
+  void add(void* ptr, int64_t words) {
+    if (!ptr || words <= 0) return;
+    p[k] = (uint32_t*)ptr;
+    n[k++] = words;
+  }
+  unsigned blocks() const {
+    int64_t most = 0;
+    for (int i = 0; i < k; ++i) most = n[i] > most ? n[i] : most;
+    const int64_t b = (most / 4 + 255) / 256;
+    return (unsigned)(b < 1 ? 1 : (b > 2048 ? 2048 : b));
+  }
+};
 
-__global__ void k_init_counters(Counters* c, uint32_t n0, WorkPart* wp) {
-  for (int i = threadIdx.x; i < (DT_MAX_DEPTH + 2) * DT_WORK_PARTS; i += blockDim.x) wp[i].next = 0;
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    for (int g = 0; g < DT_MAX_DEPTH + 2; ++g) {
-      c->count[g] = 0;
-      c->nrefl[g] = 0;
-      c->hits[g] = 0;
-      c->nmiss[g] = 0;
-    }
-    c->count[0] = n0;
-    c->dropped = 0;
+// The counters at the start of a pass: first = n0 rays in generation 0 (src NULL),
+// or the tape's (src given); the work cursors of generations g and later from 0.
+__global__ void __launch_bounds__(256) k_prepare(ClearList c, Counters* ctr, const Counters* src, int init, uint32_t n0,
+                                                 WorkPart* wp, int g) {
+  const int64_t tid = blockIdx.x * 256 + (int64_t)threadIdx.x, step = (int64_t)gridDim.x * 256;
+  for (int k = 0; k < c.k; ++k) {
+    uint32_t* p = c.p[k];
+    const int64_t n = c.n[k];
+    int64_t head = (int64_t)((16u - ((uintptr_t)p & 15u)) & 15u) / 4;
+    if (head > n) head = n;
+    const int64_t quads = (n - head) / 4, tail = head + 4 * quads;
+    for (int64_t i = tid; i < quads; i += step) ((uint4*)(p + head))[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (tid < head) p[tid] = 0u;
+    if (tail + tid < n) p[tail + tid] = 0u;
+  }
+  if (blockIdx.x != 0) return;
+  for (int i = g * DT_WORK_PARTS + threadIdx.x; i < (DT_MAX_DEPTH + 2) * DT_WORK_PARTS; i += 256) wp[i].next = 0;
+  if (!init) return;
+  constexpr int WORDS = sizeof(Counters) / 4;
+  static_assert(WORDS <= 256 && sizeof(Counters) % 4 == 0, "a word per thread");
+  const int i = threadIdx.x;
+  const int count0 = offsetof(Counters, count) / 4, miss0 = offsetof(Counters, nmiss) / 4;
+  if (i < WORDS) {
+    uint32_t v = src ? ((const uint32_t*)src)[i] : (i == count0 ? n0 : 0u);
+    if (i >= miss0 && i < miss0 + DT_MAX_DEPTH + 2) v = 0u;
+    ((uint32_t*)ctr)[i] = v;
   }
 }
 
-__global__ void k_load_counters(Counters* c, const Counters* src) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    *c = *src;
-    for (int g = 0; g < DT_MAX_DEPTH + 2; ++g) c->nmiss[g] = 0;
+// the end of a forward pass: the counters to the tape, the statistics (a value
+// per lane; one lane walking them took 4 us)
+__global__ void __launch_bounds__(64) k_finish(const Counters* c, int D, const BvhHeader* hdr, int64_t* stats,
+                                               Counters* tape) {
+  static_assert(DT_STATS_LEN == 64 && DT_MAX_DEPTH < 17, "a value per lane");
+  const int l = threadIdx.x;
+  if (tape)
+    for (int i = l; i < (int)(sizeof(Counters) / 4); i += 64) ((uint32_t*)tape)[i] = ((const uint32_t*)c)[i];
+  if (!stats) return;
+  const uint32_t n = l <= D ? c->count[l] : 0u;
+  int64_t tot = n, hits = l <= D ? c->hits[l] : 0u;
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) {
+    tot += __shfl_xor(tot, m);
+    hits += __shfl_xor(hits, m);
   }
-}
-
-__global__ void k_save_counters(Counters* dst, const Counters* c) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *dst = *c;
-}
-
-// cursors of generations g and later, before they are traced again
-__global__ void k_reset_work(int g, WorkPart* wp) {
-  for (int i = g * DT_WORK_PARTS + threadIdx.x; i < (DT_MAX_DEPTH + 2) * DT_WORK_PARTS; i += blockDim.x)
-    wp[i].next = 0;
-}
-
-__global__ void k_stats(const Counters* c, int D, const BvhHeader* hdr, int64_t* stats) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    int64_t tot = 0, gens = 0, hits = 0;
-    for (int i = 0; i < DT_STATS_LEN; ++i) stats[i] = 0;
-    for (int g = 0; g <= D; ++g) {
-      stats[g] = c->count[g];
-      stats[DT_STAT_HITS + g] = c->hits[g];
-      tot += c->count[g];
-      hits += c->hits[g];
-      if (c->count[g]) gens = g + 1;
-    }
-    stats[DT_STAT_TOTAL] = tot;
-    stats[DT_STAT_DROPPED] = c->dropped;
-    stats[DT_STAT_GENERATIONS] = gens;
-    stats[DT_STAT_BVH_DEPTH] = hdr->depth;
-    stats[DT_STAT_TOTAL_HITS] = hits;
-  }
+  const uint64_t some = __ballot(n != 0u);
+  int64_t v = n;
+  if (l >= DT_STAT_HITS && l <= DT_STAT_HITS + D) v = c->hits[l - DT_STAT_HITS];
+  if (l == DT_STAT_TOTAL) v = tot;
+  if (l == DT_STAT_DROPPED) v = c->dropped;
+  if (l == DT_STAT_GENERATIONS) v = some ? 64 - __clzll((long long)some) : 0;
+  if (l == DT_STAT_BVH_DEPTH) v = hdr->depth;
+  if (l == DT_STAT_TOTAL_HITS) v = hits;
+  stats[l] = v;
 }
 
 // ------------------------------------------------------------------ ray generation (a3)
@@ -522,20 +536,50 @@ __global__ void k_scan(Counters* ctr, int g, unsigned long long* part, unsigned 
 // scanned positions (child_positions): reflected children fill [0, n_r) of the
 // next queue, refracted children [n_r, n_r + n_t).  write_rays = 0 computes
 // indices only.  Long queues run at the rate of their 84 B a parent and 48 B a
-// child (54 us for 2 M parents, 5 TB/s).
+// child (54 us for 2 M parents, 5 TB/s).  other != NULL: a queue of at most
+// SHORT_CAP rays, whose chunk counts (not scanned) every wave adds up by itself,
+// one a lane, so that k_scan's launch (5 us) goes; the first block then does what
+// else k_scan does.
 template <bool GRID, bool FIELD>
 __global__ void __launch_bounds__(EMIT_T) k_emit(SceneDev sc, Gen q, Gen nx, int g, Counters* ctr,
                                                  const unsigned long long* part, int64_t cap_next,
-                                                 int write_rays, int32_t* flags, const float4* att) {
+                                                 int write_rays, int32_t* flags, const float4* att,
+                                                 unsigned long long* other, int64_t other_n) {
   __shared__ EmitLds lds;
   const uint32_t n = ctr->count[g];
-  const uint32_t nr_tot = ctr->nrefl[g];
+  unsigned long long mine = 0;
+  uint32_t nr_tot;
+  auto wave_sum = [](unsigned long long v) {
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) v += __shfl_xor(v, m);
+    return v;
+  };
+  if (other) {
+    static_assert(SHORT_CAP <= 64 * CHUNK, "a chunk per lane");
+    const uint32_t l = threadIdx.x & 63u;
+    mine = l * (uint32_t)CHUNK < n ? part[l] : 0ull;
+    const unsigned long long all = wave_sum(mine);
+    nr_tot = (uint32_t)all;
+    if (blockIdx.x == 0) {
+      for (int64_t i = threadIdx.x; i < other_n; i += EMIT_T) other[i] = 0ull;
+      if (threadIdx.x == 0) {
+        const uint64_t tot = (all & 0xffffffffull) + (all >> 32);
+        ctr->nrefl[g] = nr_tot;
+        ctr->count[g + 1] = (uint32_t)(tot < (uint64_t)cap_next ? tot : (uint64_t)cap_next);
+      }
+    }
+  } else {
+    nr_tot = ctr->nrefl[g];
+  }
   for (int64_t blk = blockIdx.x; blk * EMIT_T < n; blk += gridDim.x) {
     int64_t i = blk * EMIT_T + threadIdx.x;
     bool active = i < n;
     uint32_t code = active ? q.code[i] : 0u;
     bool hr = (code & C_HAS_R) != 0u, ht = (code & C_HAS_T) != 0u;
-    const uint2 at = child_positions(q.code, blk, part, nr_tot, hr, ht, lds);
+    const int64_t chunk = blk * EMIT_T / CHUNK;
+    const unsigned long long base =
+        other ? wave_sum((int64_t)(threadIdx.x & 63u) < chunk ? mine : 0ull) : part[chunk];
+    const uint2 at = child_positions(q.code, blk, base, nr_tot, hr, ht, lds);
     const uint32_t ir = at.x, it = at.y;
     if (active) {
       int cr = -1, ctd = -1;
@@ -1519,6 +1563,46 @@ __global__ void k_field_gather(FieldDev F, const float* copies, int n_copies) {
 
 // ------------------------------------------------------------------ per-face gathering
 // nodes of the generation sorted by face: node i goes to off[face] + rank
+// Places of the faces' records: off[f] = where face f's cnt[f] records go.  The
+// faces' order does not matter, so a block scans its own and takes room for them
+// from a cursor (off[nf], 0 before) in one launch, where an ordered scan took
+// three (14 us a generation for 102,400 faces, now 5).
+constexpr int FO_T = 256, FO_PER = 4;
+
+__global__ void __launch_bounds__(FO_T) k_face_offsets(int32_t nf, const uint32_t* cnt, uint32_t* off) {
+  __shared__ uint32_t waves[FO_T / 64], room;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int64_t f0 = ((int64_t)blockIdx.x * FO_T + threadIdx.x) * FO_PER;
+  uint32_t c[FO_PER], mine = 0;
+#pragma unroll
+  for (int k = 0; k < FO_PER; ++k) {
+    c[k] = f0 + k < nf ? cnt[f0 + k] : 0u;
+    mine += c[k];
+  }
+  uint32_t inc = mine;
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) {
+    const uint32_t v = __shfl_up(inc, m);
+    if (lane >= m) inc += v;
+  }
+  if (lane == 63) waves[wv] = inc;
+  __syncthreads();
+  uint32_t before = 0, all = 0;
+#pragma unroll
+  for (int k = 0; k < FO_T / 64; ++k) {
+    before += k < wv ? waves[k] : 0u;
+    all += waves[k];
+  }
+  if (threadIdx.x == 0) room = all ? atomicAdd(off + nf, all) : 0u;
+  __syncthreads();
+  uint32_t at = room + before + inc - mine;
+#pragma unroll
+  for (int k = 0; k < FO_PER; ++k) {
+    if (f0 + k < nf) off[f0 + k] = at;
+    at += c[k];
+  }
+}
+
 __global__ void k_face_scatter(const Counters* ctr, int g, const int2* fkey, const uint32_t* off,
                                uint32_t* fidx) {
   const int64_t n = ctr->count[g];
@@ -1532,17 +1616,19 @@ __global__ void k_face_scatter(const Counters* ctr, int g, const int2* fkey, con
 // Each face's records of the generation summed by a group of FG lanes and
 // added to the face's running totals fg (18 floats per face: for corner k,
 // the position adjoint then the vertex-normal adjoint); the group owns the
-// face, so no atomics.  The face's count is reset for the next generation.
+// face, so no atomics.  The face's count and the cursor are reset for the next
+// generation.
 constexpr int FG = 16;
 constexpr int FR_T = 256;
 
 __global__ void __launch_bounds__(FR_T) k_face_reduce(int32_t nf, const FaceRec* frec,
-                                                      const uint32_t* fidx, const uint32_t* off,
+                                                      const uint32_t* fidx, uint32_t* off,
                                                       uint32_t* fcnt, float* fg) {
   const int sub = threadIdx.x % FG;
+  if (blockIdx.x == 0 && threadIdx.x == 0) off[nf] = 0u;
   const int64_t groups = (int64_t)gridDim.x * (FR_T / FG);
   for (int64_t f = blockIdx.x * (int64_t)(FR_T / FG) + threadIdx.x / FG; f < nf; f += groups) {
-    const uint32_t b = off[f], e = off[f + 1];
+    const uint32_t b = off[f], e = b + fcnt[f];
     if (b == e) continue;  // the whole group agrees
     v3 p0 = mk3(0.f, 0.f, 0.f), p1 = p0, p2 = p0, n0 = p0, n1 = p0, n2 = p0;
     for (uint32_t j = b + (uint32_t)sub; j < e; j += FG) {
@@ -1620,7 +1706,8 @@ __global__ void __launch_bounds__(RED_T) k_reduce_scalars(const float4* red, int
                                                           float* d_sigma) {
   __shared__ double sh[4][RED_T];
   double a[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+#pragma unroll 8
+  for (int i = threadIdx.x; i < n; i += RED_T) {
     float4 v = red[i];
     a[0] += v.x;
     a[1] += v.y;
@@ -1958,11 +2045,12 @@ dt_status run_generation(const SceneDev& sc, const Plan& P, int g, Gen cur, Gen 
   }
   if (g < P.D) {
     int64_t other_n = (P.cap[g + 1] + CHUNK - 1) / CHUNK + 1;
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, ctr, g, part_g, part_other, other_n,
-                       P.cap[g + 1]);
+    unsigned long long* own = P.cap[g] <= SHORT_CAP ? part_other : nullptr;
+    if (!own)
+      hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, ctr, g, part_g, part_other, other_n, P.cap[g + 1]);
 #define DT_EMIT(G, FL)                                                                                 \
   hipLaunchKernelGGL((k_emit<G, FL>), dim3(emit_grid(P.cap[g])), dim3(EMIT_T), 0, s, sc, cur, nxt, g, ctr, part_g, \
-                     P.cap[g + 1], write_next, accumulate ? flags : nullptr, att)
+                     P.cap[g + 1], write_next, accumulate ? flags : nullptr, att, own, other_n)
     if (sc.fd.grid) {
       if (sc.ab.mu) DT_EMIT(true, true); else DT_EMIT(false, true);
     } else {
@@ -1974,20 +2062,9 @@ dt_status run_generation(const SceneDev& sc, const Plan& P, int g, Gen cur, Gen 
   return DT_OK;
 }
 
-dt_status zero_f32(float* p, int64_t n, hipStream_t s) {
-  if (!p || n <= 0) return DT_OK;
-  unsigned nb = dt_blocks(n, 256);
-  if (nb > 4096) nb = 4096;
-  hipLaunchKernelGGL(k_zero_f32, dim3(nb), dim3(256), 0, s, p, n);
-  DT_CHECK_LAUNCH();
-  return DT_OK;
-}
-
-dt_status zero_u64(unsigned long long* p, int64_t n, hipStream_t s) {
-  if (!p || n <= 0) return DT_OK;
-  unsigned nb = dt_blocks(n, 256);
-  if (nb > 4096) nb = 4096;
-  hipLaunchKernelGGL(k_zero_u64, dim3(nb), dim3(256), 0, s, p, n);
+dt_status prepare(const ClearList& c, Counters* ctr, const Counters* src, bool init, uint32_t n0, WorkPart* wp, int g,
+                  hipStream_t s) {
+  hipLaunchKernelGGL(k_prepare, dim3(c.blocks()), dim3(256), 0, s, c, ctr, src, init ? 1 : 0, n0, wp, g);
   DT_CHECK_LAUNCH();
   return DT_OK;
 }
@@ -2108,12 +2185,13 @@ extern "C" dt_status dt_trace_forward(const dt_scene* scene, const dt_rays* rays
   Counters* ctr = (Counters*)(W + P.w_ctr);
   unsigned long long* part[2] = {(unsigned long long*)(W + P.w_part0),
                                  (unsigned long long*)(W + P.w_part1)};
-  hipLaunchKernelGGL(k_init_counters, dim3(1), dim3(64), 0, s, ctr, (uint32_t)N, (WorkPart*)(W + P.w_parts));
-  if (dt_status st = zero_u64(part[0], P.maxchunks + 1, s)) return st;
-  if (dt_status st = zero_f32(rgb, 3 * npix, s)) return st;
-  if (dt_status st = zero_f32(wtrunc, 3 * npix, s)) return st;
-  if (dt_status st = zero_f32((float*)flags, npix, s)) return st;
-  if (dt_status st = zero_u64((unsigned long long*)path_sig, npix, s)) return st;
+  ClearList clear;
+  clear.add(part[0], 2 * (P.maxchunks + 1));
+  clear.add(rgb, 3 * npix);
+  clear.add(wtrunc, 3 * npix);
+  clear.add(flags, npix);
+  clear.add(path_sig, 2 * npix);
+  if (dt_status st = prepare(clear, ctr, nullptr, true, (uint32_t)N, (WorkPart*)(W + P.w_parts), 0, s)) return st;
 
   // where generation g lives during the forward pass: on the tape when it is
   // stored there, otherwise in the ping-pong scratch queues of the workspace
@@ -2150,8 +2228,9 @@ extern "C" dt_status dt_trace_forward(const dt_scene* scene, const dt_rays* rays
                                       (float4*)(W + P.w_adj[0][0]), s))
       return st;
   }
-  if (T) hipLaunchKernelGGL(k_save_counters, dim3(1), dim3(64), 0, s, (Counters*)(T + P.tape_hdr), ctr);
-  if (stats) hipLaunchKernelGGL(k_stats, dim3(1), dim3(64), 0, s, ctr, P.D, sc.bvh.hdr, stats);
+  if (T || stats)
+    hipLaunchKernelGGL(k_finish, dim3(1), dim3(64), 0, s, ctr, P.D, sc.bvh.hdr, stats,
+                       T ? (Counters*)(T + P.tape_hdr) : nullptr);
   DT_CHECK_LAUNCH();
   return DT_OK;
 }
@@ -2187,14 +2266,14 @@ extern "C" dt_status dt_trace_backward(const dt_scene* scene, const dt_rays* ray
   uint32_t* fidx = (uint32_t*)(W + P.w_fidx);
   uint32_t* fcnt = (uint32_t*)(W + P.w_fcnt);
   uint32_t* foff = (uint32_t*)(W + P.w_foff);
-  int32_t* fscan = (int32_t*)(W + P.w_fscan);
   float* fg = (float*)(W + P.w_fg);
   const int nred = (P.D + 1) * ADJ_MAX_BLOCKS;  // slot g * ADJ_MAX_BLOCKS + block
-  hipLaunchKernelGGL(k_load_counters, dim3(1), dim3(64), 0, s, ctr, (const Counters*)(T + P.tape_hdr));
-  if (dt_status st = zero_f32(dV, 3 * (int64_t)scene->nv, s)) return st;
-  if (dt_status st = zero_f32(dN, 3 * (int64_t)scene->nv, s)) return st;
-  if (dt_status st = zero_f32((float*)fcnt, (int64_t)scene->nf + 1, s)) return st;
-  if (dt_status st = zero_f32(fg, 18 * (int64_t)scene->nf, s)) return st;
+  ClearList clear;
+  clear.add(dV, 3 * (int64_t)scene->nv);
+  clear.add(dN, 3 * (int64_t)scene->nv);
+  clear.add(fcnt, scene->nf);
+  clear.add(foff + scene->nf, 1);  // the cursor of k_face_offsets
+  clear.add(fg, 18 * (int64_t)scene->nf);
   // absorption grid: as many copies of the per-cell records as the scratch
   // region holds (at most 64)
   const int64_t gsize = sc.ab.mu ? 3 * (int64_t)sc.ab.nx * sc.ab.ny * sc.ab.nz : 0;
@@ -2212,15 +2291,13 @@ extern "C" dt_status dt_trace_backward(const dt_scene* scene, const dt_rays* ray
       gcopies = sc.ab.d_mu;
       gcell = false;
     }
-    if (dt_status st = zero_f32(gcopies, gcell ? csize * n_copies : gsize, s)) return st;
+    clear.add(gcopies, gcell ? csize * n_copies : gsize);
   }
-  if (sc.env.d_tex)
-    if (dt_status st = zero_f32(sc.env.d_tex, 3 * (int64_t)sc.env.W * sc.env.H, s)) return st;
+  clear.add(sc.env.d_tex, 3 * (int64_t)sc.env.W * sc.env.H);
   static_assert(FG_SCRATCH >= MLP_WG_BYTES, "the second run of partial sums lies in the field's scratch");
   const MlpParts mlp_part = {{(float*)(W + P.w_mlpg), (float*)(W + P.w_fscr)}};
   if (sc.env.d_w)
-    for (int r = 0; r < 2; ++r)
-      if (dt_status st = zero_f32(mlp_part.run[r], MLP_WG_ROWS * mlp_wgrad_params(sc.env), s)) return st;
+    for (int r = 0; r < 2; ++r) clear.add(mlp_part.run[r], MLP_WG_ROWS * mlp_wgrad_params(sc.env));
   // volumetric field: as many copies of the per-cell records as the scratch
   // region holds (at most FG_MAX_COPIES); a field whose records do not fit has
   // its gradient added in place by the adjoint instead
@@ -2234,14 +2311,16 @@ extern "C" dt_status dt_trace_backward(const dt_scene* scene, const dt_rays* ray
     f_copies = (int)(fit < FG_MAX_COPIES ? fit : FG_MAX_COPIES);
     if (f_copies >= 1) {
       fseg = (float4*)(W + P.w_fseg);
-      if (dt_status st = zero_f32(fcopies, rec * f_copies, s)) return st;
+      clear.add(fcopies, rec * f_copies);
     } else {
       f_copies = 0;
-      if (dt_status st = zero_f32(sc.fd.d_grid, 4 * (int64_t)sc.fd.nx * sc.fd.ny * sc.fd.nz, s)) return st;
-      if (dt_status st = zero_f32(sc.fd.d_planes, 12 * (int64_t)sc.fd.res * sc.fd.res, s)) return st;
+      clear.add(sc.fd.d_grid, 4 * (int64_t)sc.fd.nx * sc.fd.ny * sc.fd.nz);
+      clear.add(sc.fd.d_planes, 12 * (int64_t)sc.fd.res * sc.fd.res);
     }
   }
-  if (dt_status st = zero_f32((float*)red, 4 * (int64_t)nred, s)) return st;
+  clear.add(red, 4 * (int64_t)nred);
+  if (dt_status st = prepare(clear, ctr, (const Counters*)(T + P.tape_hdr), true, 0, (WorkPart*)(W + P.w_parts), 0, s))
+    return st;
   Adj adj[2];
   for (int b = 0; b < 2; ++b) {
     adj[b].L = (float4*)(W + P.w_adj[b][0]);
@@ -2297,9 +2376,8 @@ extern "C" dt_status dt_trace_backward(const dt_scene* scene, const dt_rays* ray
         hipLaunchKernelGGL(k_grid_grad<false>, dim3((unsigned)(gb < 8192 ? gb : 8192)), dim3(GG_T), 0, s,
                            sc.ab, q, g, ctr, adj[g & 1], gcopies, n_copies);
     }
-    // fcnt[nf] stays 0, so foff[nf] is the total
-    if (dt_status st = dt_scan_exclusive_i32((const int32_t*)fcnt, (int32_t*)foff, scene->nf + 1, fscan, s))
-      return st;
+    hipLaunchKernelGGL(k_face_offsets, dim3((unsigned)((scene->nf + FO_T * FO_PER - 1) / (FO_T * FO_PER))), dim3(FO_T),
+                       0, s, scene->nf, fcnt, foff);
     hipLaunchKernelGGL(k_face_scatter, dim3(dt_blocks(P.cap[g], 256) < 8192 ? dt_blocks(P.cap[g], 256) : 8192),
                        dim3(256), 0, s, ctr, g, fkey, foff, fidx);
     const int64_t fgroups = ((int64_t)scene->nf + FR_T / FG - 1) / (FR_T / FG);
@@ -2334,8 +2412,9 @@ extern "C" dt_status dt_trace_backward(const dt_scene* scene, const dt_rays* ray
       seg[0].o = (float4*)(T + P.t_o[g0]);
       seg[0].d = (float4*)(T + P.t_d[g0]);
       seg[0].w = (float4*)(T + P.t_w[g0]);
-      hipLaunchKernelGGL(k_reset_work, dim3(1), dim3(64), 0, s, g0, (WorkPart*)(W + P.w_parts));
-      if (dt_status st = zero_u64(part[g0 & 1], P.maxchunks + 1, s)) return st;
+      ClearList again;
+      again.add(part[g0 & 1], 2 * (P.maxchunks + 1));
+      if (dt_status st = prepare(again, nullptr, nullptr, false, 0, (WorkPart*)(W + P.w_parts), g0, s)) return st;
       // adj[(g1 + 1) & 1] holds generation g1 + 1's adjoint records, which the
       // segment's first adjoint reads; adj[g1 & 1] is free until it writes
       // it, and carries the attenuation from k_trace to k_emit meanwhile

@@ -46,7 +46,7 @@ def long_trace(request):
     return scene, o, d, *_trace(scene, o, d)
 
 
-@pytest.mark.parametrize("n", [1, 7, 8, 9, 63, 65, 513, 5000, 32768, 32769])
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 63, 65, 513, 2048, 2049, 5000, 32768, 32769])
 def test_short_queue(long_trace, n):
     scene, o, d, rgb, sig = long_trace
     r, s = _trace(scene, o[:n].contiguous(), d[:n].contiguous())
