@@ -124,7 +124,10 @@ class Server:
     The loop keeps the device busy: step k + 1 is queued before the host reads
     step k's per-slot counts (copied into pinned memory behind an event), so
     host bookkeeping overlaps device work; admissions and releases act one
-    step later than they could.
+    step later than they could.  Finished images are copied out on a stream of
+    their own beside the steps (in line with them the copies took 3.1 of the 17.3
+    ms of a burst of 20 requests); a step that admits into pixels whose copy is in
+    flight waits for it.
     """
 
     MARGIN = 1.25
@@ -149,6 +152,7 @@ class Server:
         self.stats = self.info[8 * MAX_SLOTS:].view(torch.int64)
         self._host = [torch.empty(self.info.numel(), dtype=torch.uint8).pin_memory() for _ in range(2)]
         self._ev = [torch.cuda.Event() for _ in range(2)]
+        self._copies = torch.cuda.Stream(device=self.dev)
         self.t_eps = t_eps
         self.default_growth = float(default_growth)
         self.growth = {}
@@ -211,7 +215,7 @@ class Server:
         pending = collections.deque(sorted(requests, key=lambda r: r.arrival))
         waiting = collections.deque()
         active = {}            # slot -> request
-        draining = []          # (request, image, flags, sig, event): copies in flight
+        draining = []          # (request, image, flags, sig, event, first pixel, pixels): copies in flight
         free_slots = list(range(MAX_SLOTS))[::-1]
         pool = _Pool(self.n_pixels)
         reserved = 0
@@ -228,7 +232,7 @@ class Server:
         def drain(block=False):
             keep = []
             for item in draining:
-                r, img, fl, sg, e = item
+                r, img, fl, sg, e = item[:5]
                 if block:
                     e.synchronize()
                 if block or e.query():
@@ -266,6 +270,10 @@ class Server:
                 admits.append(r)
                 active[r.slot] = r
             launched = None
+            for r in admits:
+                for *_, e, a, n in draining:
+                    if r.pixel_offset < a + n and a < r.pixel_offset + r.n_pixels:
+                        tstream.wait_event(e)
             if admits or any(a.admit_step < step for a in active.values()):
                 arr = (_Admit * max(len(admits), 1))()
                 for i, r in enumerate(admits):
@@ -334,12 +342,18 @@ class Server:
                     else:
                         g = max(r.peak, r.n_pixels) / r.n_pixels
                         self.growth[r.scene] = max(self.growth.get(r.scene, 0.0), g)
-                        img = self.pixels[a:a + n].to("cpu", non_blocking=True)
-                        fl = self.flags[a:a + n].to("cpu", non_blocking=True)
-                        sg = self.sig[a:a + n].to("cpu", non_blocking=True)
-                        e = torch.cuda.Event()
-                        e.record(tstream)
-                        draining.append((r, img, fl, sg, e))
+                        # its last step is over (the report was waited for), and
+                        # later steps leave its pixels alone until they are given
+                        # to another request
+                        with torch.cuda.stream(self._copies):
+                            img = self.pixels[a:a + n].to("cpu", non_blocking=True)
+                            fl = self.flags[a:a + n].to("cpu", non_blocking=True)
+                            sg = self.sig[a:a + n].to("cpu", non_blocking=True)
+                            e = torch.cuda.Event()
+                            e.record()
+                        for t in (self.pixels, self.flags, self.sig):
+                            t.record_stream(self._copies)
+                        draining.append((r, img, fl, sg, e, a, n))
                     pool.release(a, n)
                     free_slots.append(slot)
             prev = launched
