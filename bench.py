@@ -53,13 +53,13 @@ MEASURED_TRAFFIC = {
         "sources": ["paper_2603_00413_amd/csrc/trace.hip", "paper_2603_00413_amd/csrc/dt_device.h",
                     "paper_2603_00413_amd/csrc/dt_internal.h", "paper_2603_00413_amd/csrc/dt_queue.h",
                     "paper_2603_00413_amd/csrc/bvh.hip"],
-        "sha256": "3f81142cced588f5d14840ca135c9dcc59b1b8a4dbcf75baa9ab5206c1062c94",
-        "bytes": (316911.5 * 2.0 + 79344.9) * 1024,
+        "sha256": "4d30d0f524beb36924b866a8606ae1a21143617ef74f9ec260059211048d6a7d",
+        "bytes": (270609.8 * 2.0 + 77340.9) * 1024,
         # rocprofv3 --pmc SQ_INSTS_VALU SQ_THREAD_CYCLES_VALU SQ_ACTIVE_INST_VALU:
         # wave-level VALU instructions per launch, and the share of lanes active
         # in them
-        "valu_insts": 2.605e8,
-        "lane_utilization": 0.619,
+        "valu_insts": 2.018e8,
+        "lane_utilization": 0.642,
     },
 }
 

@@ -35,7 +35,7 @@
 // layer of 16 rays is 24 products (16 x 64 of width 64) against some 100
 // instructions of splitting the activations, which therefore work on packed
 // pairs (byte permutes and the packed bf16 conversion).  1 M rays, three layers of
-// 64: 113 us with 70 % of the vector issue slots taken; four layers of 128, value
+// 64: 112 us with 66 % of the vector issue slots taken; four layers of 128, value
 // and direction gradient: 617 us (some 1,500 before, when W^T came by two-byte
 // reads and the pass ran 4 spilling waves a CU).
 #include "dt_queue.h"
