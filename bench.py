@@ -53,8 +53,8 @@ MEASURED_TRAFFIC = {
         "sources": ["paper_2603_00413_amd/csrc/trace.hip", "paper_2603_00413_amd/csrc/dt_device.h",
                     "paper_2603_00413_amd/csrc/dt_internal.h", "paper_2603_00413_amd/csrc/dt_queue.h",
                     "paper_2603_00413_amd/csrc/bvh.hip"],
-        "sha256": "4d30d0f524beb36924b866a8606ae1a21143617ef74f9ec260059211048d6a7d",
-        "bytes": (270609.8 * 2.0 + 77340.9) * 1024,
+        "sha256": "383f3845485d560767ed2615a8f21f4fc169158bcfd343f7a8696a05d941f303",
+        "bytes": (271110.7 * 2.0 + 77341.0) * 1024,
         # rocprofv3 --pmc SQ_INSTS_VALU SQ_THREAD_CYCLES_VALU SQ_ACTIVE_INST_VALU:
         # wave-level VALU instructions per launch, and the share of lanes active
         # in them
