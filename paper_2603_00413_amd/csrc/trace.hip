@@ -722,9 +722,9 @@ struct VtxAdj {
 // Adjoint of node i of generation g: writes its record (subtree radiance,
 // d/d origin, d/d direction) to cur, adds its dIoR / dsigma terms to acc and
 // returns its vertex contributions.
-// FIELD: 0 none; 1 the field's ray terms in one pass over the samples, its
-// parameters' gradient (if any) left to k_field_grad; 2 the parameters' gradient
-// added in place (fields whose records exceed the scratch region)
+// FIELD: 0 none; 1 the field's ray terms, its parameters' gradient (if any) left
+// to k_field_grad; 2 the parameters' gradient added in place (fields whose
+// records exceed the scratch region)
 template <bool GRID, int FIELD>
 __device__ __forceinline__ void adjoint_node(const SceneDev& sc, const Gen& q, int64_t i,
                                              const float* grad_rgb, const Adj& nxt, const Adj& cur,
@@ -746,25 +746,19 @@ __device__ __forceinline__ void adjoint_node(const SceneDev& sc, const Gen& q, i
     if constexpr (FIELD != 0) {
       if (!(__float_as_uint(w4.w) & RAY_INSIDE)) {
         // L = C + T E along the exterior ray
-        v3 ob = mk3(0.f, 0.f, 0.f), L;
+        v3 C;
+        float T;
+        field_segment(sc.fd, o, d, 0.f, true, C, T);
+        const v3 E = env_equirect_grad(sc.env, d, gW * T, &dd);
+        const v3 L = C + E * T;
+        v3 ob = mk3(0.f, 0.f, 0.f);
         float tb = 0.f;
+        field_segment_bwd<FIELD == 2>(sc.fd, o, d, 0.f, true, L, gW, ob, dd, tb);
         if constexpr (FIELD == 1) {
-          FieldSums fs;
-          field_segment_sums(sc.fd, o, d, 0.f, true, gW, fs);
-          const v3 E = env_equirect_grad(sc.env, d, gW * fs.T, &dd);
-          L = fs.C + E * fs.T;
-          field_sums_bwd(sc.fd, d, fs, L, gW, ob, dd, tb);
           if (fseg) {
-            fseg[2 * i] = make_float4(L.x, L.y, L.z, fs.T);
+            fseg[2 * i] = make_float4(L.x, L.y, L.z, T);
             fseg[2 * i + 1] = make_float4(gW.x, gW.y, gW.z, 2.f);  // open segment
           }
-        } else {
-          v3 C;
-          float T;
-          field_segment(sc.fd, o, d, 0.f, true, C, T);
-          const v3 E = env_equirect_grad(sc.env, d, gW * T, &dd);
-          L = C + E * T;
-          field_segment_bwd(sc.fd, o, d, 0.f, true, L, gW, ob, dd, tb);
         }
         cur.L[i] = make_float4(L.x, L.y, L.z, 0.f);
         cur.O[i] = make_float4(ob.x, ob.y, ob.z, 0.f);
@@ -792,16 +786,8 @@ __device__ __forceinline__ void adjoint_node(const SceneDev& sc, const Gen& q, i
   HitGeo geo = load_geo(sc, tri);
   // with the grid, the interior segment's attenuation and its adjoint sums
   // come from one pass over its samples (shade<false> leaves A to it)
-  Shade s = shade<false, FIELD == 2>(sc, geo, o, d, t, b1, b2, code);
+  Shade s = shade<false, FIELD != 0>(sc, geo, o, d, t, b1, b2, code);
   const bool entering = (code & C_ENTER) != 0u, tir = (code & C_TIR) != 0u;
-  FieldSums fs;
-  if constexpr (FIELD == 1) {
-    if (field_seg) {
-      field_segment_sums(sc.fd, o, d, t, false, gW, fs);
-      s.A = mk3(fs.T, fs.T, fs.T);
-      s.Cem = fs.C;
-    }
-  }
   TauSums ts;
   if constexpr (GRID) {
     if (!entering) {
@@ -910,14 +896,12 @@ __device__ __forceinline__ void adjoint_node(const SceneDev& sc, const Gen& q, i
       L = L + s.Cem;
       // the segment's radiance C + T M (A = T here)
       const v3 Lseg = s.Cem + Mf * s.A.x;
+      field_segment_bwd<FIELD == 2>(sc.fd, o, d, t, false, Lseg, gW, oabs, dbar, tbar);
       if constexpr (FIELD == 1) {
-        field_sums_bwd(sc.fd, d, fs, Lseg, gW, oabs, dbar, tbar);
         if (fseg) {
           fseg[2 * i] = make_float4(Lseg.x, Lseg.y, Lseg.z, t);
           fseg[2 * i + 1] = make_float4(gW.x, gW.y, gW.z, 1.f);  // closed segment [0, t]
         }
-      } else {
-        field_segment_bwd(sc.fd, o, d, t, false, Lseg, gW, oabs, dbar, tbar);
       }
     }
   }
