@@ -35,10 +35,11 @@ struct SmoothWs {
   double* r;        // [nv][3] the carried residual; else the other iterate (even steps write the caller's x)
   double* d[2];     // [nv][3] carried: corrections, iteration k reads d[k & 1] and writes d[(k + 1) & 1]
   double* part;     // [2][blocks][3] partial b . b and r . r
-  double* bmax;     // [blocks] largest eigenvalue bound of the block's vertices
   double* sums;     // [8]: b . b, r . r per column; [6] the bound m
+  // in the corrections' room until a carried recurrence takes it:
   int4* nbr;        // [nv][2] the first NBR neighbours of each vertex (itself where there are fewer)
   int* deg;         // [nv] degrees
+  double* bmax;     // [blocks] largest eigenvalue bound of the block's vertices
 };
 
 constexpr int NBR = 8;
@@ -57,10 +58,11 @@ size_t smooth_layout(int32_t nv, SmoothWs* w, char* base) {
   t.d[1] = take(3 * (size_t)nv * sizeof(double));
   const size_t nb = dt_blocks(nv, ST);
   t.part = take(6 * nb * sizeof(double));
-  t.bmax = take(nb * sizeof(double));
   t.sums = take(8 * sizeof(double));
-  t.nbr = (int4*)take(NBR * sizeof(int) * (size_t)nv);
-  t.deg = (int*)take(sizeof(int) * (size_t)nv);
+  // 36 bytes a vertex and 8 a block, of the 48 a vertex that the corrections hold
+  t.nbr = (int4*)t.d[0];
+  t.deg = base ? (int*)(t.nbr + 2 * (size_t)nv) : nullptr;
+  t.bmax = base ? (double*)(t.deg + 2 * (((size_t)nv + 1) / 2)) : nullptr;
   if (w) *w = t;
   return o;
 }
@@ -105,17 +107,33 @@ struct D3 {
 __device__ __forceinline__ D3 load_d3(const double* p, int64_t i) { return ((const D3*)p)[i]; }
 __device__ __forceinline__ double comp(const D3& v, int c) { return c == 0 ? v.x : (c == 1 ? v.y : v.z); }
 
+// the first NBR neighbours of vertex i (itself where there are fewer); its degree
+__device__ __forceinline__ int first_neighbours(const int32_t* off, const int32_t* adj, int i, int j[NBR]) {
+  const int a = off[i], deg = off[i + 1] - a;
+#pragma unroll
+  for (int k = 0; k < NBR; ++k) j[k] = k < deg ? adj[a + k] : i;
+  return deg;
+}
+
 // y = (I + lambda L) v at vertex i, (1 + lambda deg) v_i - lambda sum_j v_j, and
-// v_i.  A vertex's first NBR neighbours come from the table that the solve's
-// first kernel makes of the adjacency, so a step waits for one table read and
-// one round of value reads; walking the list, offsets, then index by index each
-// with its value, was most of a step's 10.9 us.
+// v_i.  TABLE: a vertex's first NBR neighbours come from the table that the
+// solve's first kernel makes of the adjacency, so a step waits for one table read
+// and one round of value reads; else (the carried recurrence has taken the
+// table's room) from the lists, all their indices at once.  Walking the list
+// index by index, each with its value, was most of a step's 10.9 us.
+template <bool TABLE>
 __device__ __forceinline__ void apply_row(const int32_t* off, const int32_t* adj, const SmoothWs& w, int i,
                                           double lambda, const double* v, D3& vi, double y[3]) {
-  const int deg = w.deg[i];
-  const int4 j0 = w.nbr[2 * (size_t)i], j1 = w.nbr[2 * (size_t)i + 1];
+  int deg, j[NBR];
   vi = load_d3(v, i);
-  const int j[NBR] = {j0.x, j0.y, j0.z, j0.w, j1.x, j1.y, j1.z, j1.w};
+  if constexpr (TABLE) {
+    deg = w.deg[i];
+    const int4 j0 = w.nbr[2 * (size_t)i], j1 = w.nbr[2 * (size_t)i + 1];
+    j[0] = j0.x, j[1] = j0.y, j[2] = j0.z, j[3] = j0.w;
+    j[4] = j1.x, j[5] = j1.y, j[6] = j1.z, j[7] = j1.w;
+  } else {
+    deg = first_neighbours(off, adj, i, j);
+  }
   D3 n[NBR];
 #pragma unroll
   for (int k = 0; k < NBR; ++k) n[k] = load_d3(v, j[k]);
@@ -145,17 +163,13 @@ __device__ __forceinline__ void apply_row(const int32_t* off, const int32_t* adj
 __global__ void __launch_bounds__(ST) k_sm_table(const int32_t* off, const int32_t* adj, int nv, SmoothWs w) {
   const int i = blockIdx.x * ST + threadIdx.x;
   if (i >= nv) return;
-  const int a = off[i], deg = off[i + 1] - a;
   int j[NBR];
-#pragma unroll
-  for (int k = 0; k < NBR; ++k) j[k] = k < deg ? adj[a + k] : i;
-  w.deg[i] = deg;
+  w.deg[i] = first_neighbours(off, adj, i, j);
   w.nbr[2 * (size_t)i] = make_int4(j[0], j[1], j[2], j[3]);
   w.nbr[2 * (size_t)i + 1] = make_int4(j[4], j[5], j[6], j[7]);
 }
 
-// r = b - A x, and a copy of r in d[0] (the first correction is r / theta,
-// scaled where it is read); partials of b . b (part[0 .. nb)) and r . r
+// r = b - A x; partials of b . b (part[0 .. nb)) and r . r
 // (part[nb .. 2 nb)), and the largest eigenvalue bound of the block's vertices
 __global__ void __launch_bounds__(ST) k_sm_init(const int32_t* off, const int32_t* adj, int nv, double lambda,
                                                 const double* b, const double* x, SmoothWs w) {
@@ -164,11 +178,10 @@ __global__ void __launch_bounds__(ST) k_sm_init(const int32_t* off, const int32_
   if (i < nv) {
     double ax[3];
     D3 xi;
-    apply_row(off, adj, w, i, lambda, x, xi, ax);
+    apply_row<true>(off, adj, w, i, lambda, x, xi, ax);
     const D3 bi = load_d3(b, i);
     const D3 r = {bi.x - ax[0], bi.y - ax[1], bi.z - ax[2]};
     ((D3*)w.r)[i] = r;
-    ((D3*)w.d[0])[i] = r;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
       bb[c] = comp(bi, c) * comp(bi, c);
@@ -202,7 +215,7 @@ __global__ void __launch_bounds__(ST) k_sm_norm(const int32_t* off, const int32_
     if (x) {
       double ax[3];
       D3 xi;
-      apply_row(off, adj, w, i, lambda, x, xi, ax);
+      apply_row<true>(off, adj, w, i, lambda, x, xi, ax);
       const D3 bi = load_d3(b, i);
       r = {bi.x - ax[0], bi.y - ax[1], bi.z - ax[2]};
     } else {
@@ -261,14 +274,14 @@ __global__ void __launch_bounds__(ST) k_sm_step(const int32_t* off, const int32_
   if (!first) p = load_d3(prev, i);
   double ax[3];
   D3 xi;
-  apply_row(off, adj, w, i, lambda, x, xi, ax);
+  apply_row<true>(off, adj, w, i, lambda, x, xi, ax);
   if (first) p = xi;
   ((D3*)prev)[i] = {xi.x + c1 * (xi.x - p.x) + c2 * (bi.x - ax[0]), xi.y + c1 * (xi.y - p.y) + c2 * (bi.y - ax[1]),
                     xi.z + c1 * (xi.z - p.z) + c2 * (bi.z - ax[2])};
 }
 
 // The step with the residual carried: x += d, r -= A d, dn = c1 d + c2 r (the new
-// r).  first: d holds r and the correction is r / theta.
+// r).  first: d holds a copy of r (over the table) and the correction is r / theta.
 __global__ void __launch_bounds__(ST) k_sm_step_carry(const int32_t* off, const int32_t* adj, int nv, double lambda,
                                                       int first, double inv_theta, const double* d, double* dn,
                                                       double c1, double c2, double* x, SmoothWs w) {
@@ -278,7 +291,7 @@ __global__ void __launch_bounds__(ST) k_sm_step_carry(const int32_t* off, const 
   const D3 xi = load_d3(x, i), ri = load_d3(w.r, i);
   double ad[3];
   D3 di;
-  apply_row(off, adj, w, i, lambda, d, di, ad);
+  apply_row<false>(off, adj, w, i, lambda, d, di, ad);
   const D3 dk = {sc * di.x, sc * di.y, sc * di.z};
   ((D3*)x)[i] = {xi.x + dk.x, xi.y + dk.y, xi.z + dk.z};
   const D3 r = {ri.x - sc * ad[0], ri.y - sc * ad[1], ri.z - sc * ad[2]};
@@ -364,6 +377,8 @@ extern "C" dt_status dt_smooth_solve(const int32_t* adj_off, const int32_t* adj,
   const unsigned grid = (unsigned)(nb + DIES - 1) / DIES * DIES;
   double* const xs[2] = {x, w.r};  // not carried: step it reads xs[(it - 1) & 1] and writes xs[it & 1]
   double d1 = 0.0, d2 = 1.0 / theta;  // not carried: this step's c1, c2
+  const dim3 all3(dt_blocks(3 * (int64_t)nv, ST));
+  if (carry && !done) hipLaunchKernelGGL(k_sm_copy, all3, dim3(ST), 0, s, w.d[0], w.r, 3 * (int64_t)nv);
   while (!done && it < max_iters) {
     double c1 = 0.0, c2 = 0.0;  // carried: the next correction's; else the next step's
     if (!single) {
@@ -392,7 +407,7 @@ extern "C" dt_status dt_smooth_solve(const int32_t* adj_off, const int32_t* adj,
     }
   }
   if (!carry && (it & 1))  // the last iterate lies in the workspace
-    hipLaunchKernelGGL(k_sm_copy, dim3(dt_blocks(3 * (int64_t)nv, ST)), dim3(ST), 0, s, x, w.r, 3 * (int64_t)nv);
+    hipLaunchKernelGGL(k_sm_copy, all3, dim3(ST), 0, s, x, w.r, 3 * (int64_t)nv);
   DT_CHECK_LAUNCH();
   if (iters_out) *iters_out = it;
   if (resid_out) *resid_out = sqrt(worst);
