@@ -373,7 +373,11 @@ extern "C" dt_status dt_smooth_solve(const int32_t* adj_off, const int32_t* adj,
   }
   // on the iterates while the amplified rounding, some condition^(3/2) u (3e-8 at
   // 4e5 is once that), stays a factor of 32 below the tolerance
-  const bool carry = 32.0 * hi * sqrt(hi) * 1.1102230246251565e-16 > tol;
+  // (carried also where x shares memory with b, which only the first kernel reads
+  // then: each step on the iterates reads b anew)
+  const bool shared = (const char*)b < (const char*)(x + 3 * (size_t)nv) &&
+                      (const char*)x < (const char*)(b + 3 * (size_t)nv);
+  const bool carry = shared || 32.0 * hi * sqrt(hi) * 1.1102230246251565e-16 > tol;
   const unsigned grid = (unsigned)(nb + DIES - 1) / DIES * DIES;
   double* const xs[2] = {x, w.r};  // not carried: step it reads xs[(it - 1) & 1] and writes xs[it & 1]
   double d1 = 0.0, d2 = 1.0 / theta;  // not carried: this step's c1, c2
