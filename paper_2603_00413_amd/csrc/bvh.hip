@@ -1205,10 +1205,12 @@ extern "C" dt_status dt_build_bvh(const float* V, int32_t nv, const int32_t* F, 
   hipLaunchKernelGGL(k_vfill, dim3(dt_blocks(nf, 256)), dim3(256), 0, s, F, nf, nv, off, rank, idx);
   hipLaunchKernelGGL(k_vnormals, dim3(dt_blocks(nv, 256)), dim3(256), 0, s, off, idx, fn, nv, vn);
   DT_CHECK_LAUNCH();
-  // Morton order and the binary tree.  Up to 2^23 triangles the top 32 bits of
+  // Morton order and the binary tree.  Up to 2^20 triangles the top 32 bits of
   // the code (2,048 cells an axis) order them finely enough (ties fall back to
-  // the face index) and halve the sort: a 2 M face wall's tree has the same
-  // node visits with 64, 32 or 29 bits
+  // the face index) and halve the sort.  Above, an even mesh's tree has the same
+  // node visits with 32 bits and is built sooner (2 M faces 1.57 against 1.86 ms),
+  // but one whose detail fills a small part of its box shares cells: with a piece
+  // 10^4 units away, two views of 1.2 M faces take 8.1 ms with 32 bits, 1.9 with 63
   hipLaunchKernelGGL(k_bounds, dim3(NBB), dim3(256), 0, s, V, F, nf, nv, w.bpart);
   int32_t* vi = nullptr;
   int4* topo = (int4*)w.acc;
@@ -1219,7 +1221,7 @@ extern "C" dt_status dt_build_bvh(const float* V, int32_t nv, const int32_t* F, 
     // histograms: a pass 27 -> 17 us.  The histogram, a word per four keys, sits
     // where the links go afterwards
     st = sort_and_link<uint32_t, 4>(V, F, nf, nv, 31, w, (int32_t*)w.acc, hdr, topo, lpar, &vi, s);
-  } else if (nf <= (1 << 23)) {
+  } else if (nf <= (1 << 20)) {
     st = sort_and_link<uint32_t, RS_ITEMS>(V, F, nf, nv, 31, w, w.hist, hdr, topo, lpar, &vi, s);
   } else {
     st = sort_and_link<uint64_t, RS_ITEMS>(V, F, nf, nv, 0, w, w.hist, hdr, topo, lpar, &vi, s);
