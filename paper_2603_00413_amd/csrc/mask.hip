@@ -18,7 +18,7 @@
 // projection, and a point moves with its two vertices with weights 1 - t_k
 // and t_k.
 //
-// Kernels: k_mask_forward casts the pixel-centre rays, a wave per 8 x 8 tile;
+// Kernels: k_mask_forward casts the pixel-centre rays, a wave per tile of 64;
 // k_mask_facing decides for every face which cameras it faces (in FP64:
 // products of FP32 inputs are exact, so the decision matches an FP64
 // evaluation); k_mask_grad finds the silhouette edges (an edge is taken by the
@@ -97,15 +97,32 @@ __device__ __forceinline__ bool project(const CamDev& c, v3 X, float& xi, float&
   return true;
 }
 
-// one wave per 8 x 8 pixel tile, so a wave's rays walk the same nodes
+// Tiles of 64 pixels, 8 x 8 so that a wave's rays walk the same nodes; narrow
+// images take tiles of their own width or height, so that most lanes have a pixel
+// (and 64 times the tiles of any image stay below a launch's 2^32 threads)
+struct MaskTile {
+  int lx, ly;   // log2 of width and height
+  int64_t tw, n;
+};
+__host__ __device__ __forceinline__ int ceil_log2_8(int v) { return v >= 5 ? 3 : (v >= 3 ? 2 : v - 1); }
+__host__ __device__ __forceinline__ MaskTile mask_tile(int W, int H) {
+  MaskTile t;
+  t.lx = W < 8 ? ceil_log2_8(W) : 6 - ceil_log2_8(H);
+  t.ly = 6 - t.lx;
+  t.tw = ((int64_t)W + (1 << t.lx) - 1) >> t.lx;
+  t.n = t.tw * (((int64_t)H + (1 << t.ly) - 1) >> t.ly);
+  return t;
+}
+
 __global__ void __launch_bounds__(64) k_mask_forward(BvhView bv, MaskCams cams, float t_eps, float* mask) {
   __shared__ MaskLds lds;
   const CamDev& c = cams.c[blockIdx.y];
-  const int tw = (c.W + 7) >> 3, th = (c.H + 7) >> 3;
+  const MaskTile t = mask_tile(c.W, c.H);
   const int64_t tile = blockIdx.x;
-  if (tile >= (int64_t)tw * th) return;
+  if (tile >= t.n) return;
   const int lane = (int)threadIdx.x;
-  const int x = (int)(tile % tw) * 8 + (lane & 7), y = (int)(tile / tw) * 8 + (lane >> 3);
+  const int64_t x = (tile % t.tw) * (1 << t.lx) + (lane & ((1 << t.lx) - 1));
+  const int64_t y = (tile / t.tw) * (1 << t.ly) + (lane >> t.lx);
   const bool in = x < c.W && y < c.H;
   const float px = (2.0f * ((float)x + 0.5f) / (float)c.W - 1.0f) * c.th * c.aspect;
   const float py = (1.0f - 2.0f * ((float)y + 0.5f) / (float)c.H) * c.th;
@@ -113,7 +130,7 @@ __global__ void __launch_bounds__(64) k_mask_forward(BvhView bv, MaskCams cams, 
                           mk3(c.u[0], c.u[1], c.u[2]) * py);
   bool ovf = false;
   const bool hit = lines_blocked(bv, in, mk3(c.eye[0], c.eye[1], c.eye[2]), d, -1, -1, t_eps, lds, &ovf);
-  if (in) mask[c.pixel_offset + (int64_t)y * c.W + x] = hit ? 1.0f : 0.0f;
+  if (in) mask[c.pixel_offset + y * c.W + x] = hit ? 1.0f : 0.0f;
 }
 
 // A silhouette edge of one camera in image space: its vertices a < b, the
@@ -344,7 +361,7 @@ extern "C" dt_status dt_mask_forward(const dt_scene* sc, const dt_rays* rays, fl
   hipStream_t s = (hipStream_t)stream;
   int64_t most = 1;  // tiles of the largest image
   for (int c = 0; c < mc.n; ++c)
-    most = std::max<int64_t>(most, (int64_t)((mc.c[c].W + 7) / 8) * ((mc.c[c].H + 7) / 8));
+    most = std::max<int64_t>(most, mask_tile(mc.c[c].W, mc.c[c].H).n);
   hipLaunchKernelGGL(k_mask_forward, dim3((unsigned)most, mc.n), dim3(64), 0, s, bv, mc, t_eps, mask);
   DT_CHECK_LAUNCH();
   return DT_OK;
