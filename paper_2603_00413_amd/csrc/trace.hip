@@ -1672,11 +1672,19 @@ __device__ __forceinline__ void for_faces(const BvhView& bv, int v, F fn) {
   }
 }
 
+// the launch: VG times the vertices may be more threads than a launch holds, so
+// past VG_BLOCKS the groups take several vertices
+constexpr int64_t VG_BLOCKS = (int64_t)1 << 22;
+inline unsigned vertex_blocks(int32_t nv) {
+  const int64_t b = ((int64_t)nv * VG + 255) / 256;
+  return (unsigned)(b < VG_BLOCKS ? b : VG_BLOCKS);
+}
+
 __global__ void __launch_bounds__(256) k_vertex_gather(BvhView bv, const int32_t* F, const float* fg, float* dV,
                                                        float4* sbar) {
-  const int64_t v = (blockIdx.x * (int64_t)256 + threadIdx.x) / VG;
-  v3 p = mk3(0.f, 0.f, 0.f), nn = p;
-  if (v < bv.nv)
+  const int64_t step = (int64_t)gridDim.x * (256 / VG);
+  for (int64_t v = (blockIdx.x * (int64_t)256 + threadIdx.x) / VG; v < bv.nv; v += step) {
+    v3 p = mk3(0.f, 0.f, 0.f), nn = p;
     for_faces(bv, (int)v, [&](int f) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
@@ -1686,13 +1694,14 @@ __global__ void __launch_bounds__(256) k_vertex_gather(BvhView bv, const int32_t
         nn += mk3(q[3], q[4], q[5]);
       }
     });
-  p = vertex_sum(p);
-  nn = vertex_sum(nn) * (1.0f / 3.0f);
-  if (v >= bv.nv || threadIdx.x % VG) return;
-  dV[3 * v] = p.x;
-  dV[3 * v + 1] = p.y;
-  dV[3 * v + 2] = p.z;
-  sbar[v] = make_float4(nn.x, nn.y, nn.z, 0.f);
+    p = vertex_sum(p);
+    nn = vertex_sum(nn) * (1.0f / 3.0f);
+    if (threadIdx.x % VG) continue;
+    dV[3 * v] = p.x;
+    dV[3 * v + 1] = p.y;
+    dV[3 * v + 2] = p.z;
+    sbar[v] = make_float4(nn.x, nn.y, nn.z, 0.f);
+  }
 }
 
 // dIoR, dsigma = ordered sums of the per-(generation, block) partials
@@ -1777,9 +1786,9 @@ __global__ void __launch_bounds__(LB) k_list_misses(Gen q, int g, Counters* ctr,
 // 484 -> 79 us for 2 M.
 __global__ void __launch_bounds__(256) k_nbwd(BvhView bv, const float* V, const int32_t* F, const float4* sbar,
                                               float* dV) {
-  const int64_t v = (blockIdx.x * (int64_t)256 + threadIdx.x) / VG;
-  v3 g = mk3(0.f, 0.f, 0.f);
-  if (v < bv.nv)
+  const int64_t step = (int64_t)gridDim.x * (256 / VG);
+  for (int64_t v = (blockIdx.x * (int64_t)256 + threadIdx.x) / VG; v < bv.nv; v += step) {
+    v3 g = mk3(0.f, 0.f, 0.f);
     for_faces(bv, (int)v, [&](int f) {
       const float4 u4 = bv.fn[f];
       if (u4.w == 0.f) return;
@@ -1794,11 +1803,12 @@ __global__ void __launch_bounds__(256) k_nbwd(BvhView bv, const float* V, const 
       if (i2 == (int)v) g += e2b;
       if (i0 == (int)v) g += -(e1b + e2b);
     });
-  g = vertex_sum(g);
-  if (v >= bv.nv || threadIdx.x % VG) return;
-  dV[3 * v] += g.x;
-  dV[3 * v + 1] += g.y;
-  dV[3 * v + 2] += g.z;
+    g = vertex_sum(g);
+    if (threadIdx.x % VG) continue;
+    dV[3 * v] += g.x;
+    dV[3 * v + 1] += g.y;
+    dV[3 * v + 2] += g.z;
+  }
 }
 
 // ------------------------------------------------------------------ env / intersect kernels
@@ -2450,7 +2460,7 @@ extern "C" dt_status dt_trace_backward(const dt_scene* scene, const dt_rays* ray
   if (n_copies > 0 && gcell)
     hipLaunchKernelGGL(k_grid_gather, dim3(dt_blocks(gsize, 256) < 4096 ? dt_blocks(gsize, 256) : 4096), dim3(256),
                        0, s, gcopies, n_copies, sc.ab.nx, sc.ab.ny, sc.ab.nz, sc.ab.d_mu);
-  const unsigned vblocks = dt_blocks((int64_t)scene->nv * VG, 256);
+  const unsigned vblocks = vertex_blocks(scene->nv);
   hipLaunchKernelGGL(k_vertex_gather, dim3(vblocks), dim3(256), 0, s, sc.bvh, sc.F, fg, dV, sbar);
   hipLaunchKernelGGL(k_nbwd, dim3(vblocks), dim3(256), 0, s, sc.bvh, sc.V, sc.F, sbar, dV);
   DT_CHECK_LAUNCH();
