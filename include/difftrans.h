@@ -396,7 +396,8 @@ dt_status dt_smooth_solve(const int32_t* adj_off, const int32_t* adj, int32_t nv
  * varies run to run).  counts: device uint64 [3] or NULL: outline points in
  * an image whose pixel has a nonzero dLoss/dM, of those the visible ones,
  * and traversal stack overflows (such a point is treated as hidden).  ws:
- * dt_mask_bytes long (the edge list). */
+ * dt_mask_bytes long (which of the call's cameras each face faces, one uint16 a
+ * face). */
 #define DT_MASK_MAX_CAMERAS 16
 dt_status dt_mask_bytes(int32_t nv, int32_t nf, size_t* ws_bytes);
 dt_status dt_mask_forward(const dt_scene* sc, const dt_rays* rays, float t_eps, float* mask,

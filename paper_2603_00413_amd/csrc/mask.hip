@@ -342,12 +342,15 @@ dt_status mask_setup(const dt_scene* sc, const dt_rays* rays, BvhView& bv, MaskC
   return DT_OK;
 }
 
+// the backward's workspace: the faces' facing bits
+size_t mask_ws_bytes(int32_t nf) { return dt_align(sizeof(uint16_t) * (size_t)nf); }
+
 }  // namespace
 
 extern "C" dt_status dt_mask_bytes(int32_t nv, int32_t nf, size_t* ws_bytes) {
   DT_REQUIRE(ws_bytes, "dt_mask_bytes: NULL argument");
   DT_REQUIRE(nv >= 3 && nf >= 1 && nf <= DT_MAX_FACES, "dt_mask_bytes: need nv >= 3, 1 <= nf <= 2^26");
-  *ws_bytes = dt_align(sizeof(int4) * 3 * (size_t)nf);
+  *ws_bytes = mask_ws_bytes(nf);
   return DT_OK;
 }
 
@@ -375,7 +378,7 @@ extern "C" dt_status dt_mask_backward(const dt_scene* sc, const dt_rays* rays, c
   if (dt_status st = mask_setup(sc, rays, bv, mc)) return st;
   DT_REQUIRE(grad_mask && dV && ws, "dt_mask_backward: NULL argument");
   DT_REQUIRE(rho > 0.f && rho <= 4096.f, "rho must be in (0, 4096]");
-  const size_t need = dt_align(sizeof(int4) * 3 * (size_t)sc->nf);
+  const size_t need = mask_ws_bytes(sc->nf);
   if (ws_bytes < need) {
     dt_set_error("dt_mask_backward: workspace has %zu bytes, needs %zu", ws_bytes, need);
     return DT_ERR_WORKSPACE_TOO_SMALL;
