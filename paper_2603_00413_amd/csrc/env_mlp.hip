@@ -752,11 +752,14 @@ __global__ void k_mlp_wg_reduce(MlpParts part, int64_t n_params, int64_t n_weigh
 #define DT_MLP_SHAPES(X) X(64, 1) X(64, 2) X(64, 3) X(64, 4) X(128, 1) X(128, 2) X(128, 3) X(128, 4)
 
 // enough blocks to cover n items (16 per wave), at most those that are resident
-// together: each copies the network once
-unsigned mlp_blocks(int64_t n, int hidden) {
+// together: each copies the network once.  A network of one layer holds so few
+// registers and so little LDS that three blocks share a CU, and copies so little
+// that a fourth in line costs nothing (8 M directions, 512 or 256 blocks against
+// 1,024: width 64 316 and 291 us, width 128 557 and 441)
+unsigned mlp_blocks(int64_t n, int hidden, int layers) {
   int64_t per = MLP_T / 4;  // 16 items per wave
   int64_t b = (n + per - 1) / per;
-  const int64_t cap = hidden == 64 ? 512 : 256;
+  const int64_t cap = layers == 1 ? 1024 : (hidden == 64 ? 512 : 256);
   return (unsigned)(b < 1 ? 1 : (b > cap ? cap : b));
 }
 
@@ -775,7 +778,7 @@ bool mlp_supported(const EnvDev& e) {
   }
 
 dt_status mlp_query(const EnvDev& e, const float* dirs, int64_t n, float* rgb, hipStream_t s) {
-#define X(H, L) DT_LAUNCH(H, L, k_mlp_query, mlp_blocks(n, H), e, dirs, n, rgb)
+#define X(H, L) DT_LAUNCH(H, L, k_mlp_query, mlp_blocks(n, H, L), e, dirs, n, rgb)
   DT_MLP_SHAPES(X)
 #undef X
   dt_set_error("environment MLP shape (hidden %d, layers %d) is not supported", e.hidden, e.n_layers);
@@ -784,7 +787,7 @@ dt_status mlp_query(const EnvDev& e, const float* dirs, int64_t n, float* rgb, h
 
 dt_status mlp_query_backward(const EnvDev& e, const float* dirs, int64_t n, const float* g,
                              float* gd, hipStream_t s) {
-#define X(H, L) DT_LAUNCH(H, L, k_mlp_query_bwd, mlp_blocks(n, H), e, dirs, n, g, gd)
+#define X(H, L) DT_LAUNCH(H, L, k_mlp_query_bwd, mlp_blocks(n, H, L), e, dirs, n, g, gd)
   DT_MLP_SHAPES(X)
 #undef X
   dt_set_error("environment MLP shape (hidden %d, layers %d) is not supported", e.hidden, e.n_layers);
@@ -793,7 +796,7 @@ dt_status mlp_query_backward(const EnvDev& e, const float* dirs, int64_t n, cons
 
 dt_status mlp_trace_forward(const EnvDev& e, Gen q, const uint32_t* list, const Counters* ctr,
                             int g, int64_t cap, float* rgb, hipStream_t s) {
-#define X(H, L) DT_LAUNCH(H, L, k_mlp_trace_fwd, mlp_blocks(cap, H), e, q, list, ctr, g, rgb)
+#define X(H, L) DT_LAUNCH(H, L, k_mlp_trace_fwd, mlp_blocks(cap, H, L), e, q, list, ctr, g, rgb)
   DT_MLP_SHAPES(X)
 #undef X
   dt_set_error("environment MLP shape (hidden %d, layers %d) is not supported", e.hidden, e.n_layers);
@@ -832,7 +835,7 @@ dt_status mlp_trace_backward_wgrad(const EnvDev& e, Gen q, const uint32_t* list,
 
 dt_status mlp_trace_backward(const EnvDev& e, Gen q, const uint32_t* list, const Counters* ctr,
                              int g, int64_t cap, const float* grad_rgb, Adj cur, hipStream_t s) {
-#define X(H, L) DT_LAUNCH(H, L, k_mlp_trace_bwd, mlp_blocks(cap, H), e, q, list, ctr, g, grad_rgb, cur)
+#define X(H, L) DT_LAUNCH(H, L, k_mlp_trace_bwd, mlp_blocks(cap, H, L), e, q, list, ctr, g, grad_rgb, cur)
   DT_MLP_SHAPES(X)
 #undef X
   dt_set_error("environment MLP shape (hidden %d, layers %d) is not supported", e.hidden, e.n_layers);
