@@ -166,28 +166,45 @@ __device__ __forceinline__ bool silhouette_edge(const float* V, const int32_t* F
   return true;
 }
 
-// One wave takes MASK_SLOTS edge slots (slot 3 f + k: face f's edge from its
-// corner k) for all cameras.  Silhouette edges are a percent or so of all
-// (edge, camera) pairs and carry the only costly work, so the wave first
-// collects them in LDS and then deals their quadrature points to its lanes
-// (a thread per (edge, camera) that walked the tree for its own points left
-// one lane in fifty busy: 1,172 against 204 us for 8 views of 512 x 512 and
-// 102,400 faces).
+// One wave takes `per` edge slots (slot 3 f + k: face f's edge from its corner k)
+// for the cameras of its group (blockIdx.y, every gridDim.y-th camera).
+// Silhouette edges are a percent or so of all (edge, camera) pairs of a closed
+// mesh and carry the only costly work, so the wave first collects them in LDS and
+// then deals their quadrature points to its lanes (a thread per (edge, camera)
+// that walked the tree for its own points left one lane in fifty busy: 1,900
+// against 243 us for 8 views of 512 x 512 and 102,400 faces).
 // counts: [0] outline points in an image where the loss gradient is nonzero,
 // [1] of those, points on the outline (visible), [2] stack overflows
-constexpr int MASK_SLOTS = 256;
+// How a call is cut into waves.  On an open mesh every boundary edge is on the
+// outline of every camera, and a wave that holds many of them works on them one
+// after the other while the chip waits, so up to MASK_SMALL slots a wave takes 64
+// and a quarter of the cameras; above, there are waves enough, and 128 slots with
+// all cameras look for an edge's other face least often.  8 views of 512 x 512, 256
+// slots and all cameras / 64 and a quarter / 128 and all: 20,000 separate
+// triangles 28.9 / 3.6 / 16.0 ms (14.0 a thread per edge and camera), an open plane
+// of 80,000 faces 639 / 102 / 341 us (173), a torus of 102,400 288 / 243 / 272, of
+// 1 M 584 / 1,073 / 592
+constexpr int64_t MASK_SMALL = (int64_t)1 << 19;
+struct MaskCut {
+  int per, groups;
+};
+MaskCut mask_cut(int64_t slots, int cams) {
+  if (slots > MASK_SMALL) return {128, 1};
+  return {64, cams < 4 ? cams : 4};
+}
 constexpr int MASK_ITEMS = 128;  // collected edges per round of points
 
 __global__ void __launch_bounds__(64) k_mask_grad(const float* V, const int32_t* F, int32_t nv, int32_t nf,
                                                   BvhView bv, const uint16_t* facing, MaskCams cams,
                                                   const float* grad_mask, float rho, float* dV,
-                                                  unsigned long long* counts) {
+                                                  unsigned long long* counts, int per) {
   __shared__ MaskLds lds;
   __shared__ int4 item[MASK_ITEMS];                      // slot, other face or -1, camera, front face
   __shared__ unsigned long long first[MASK_ITEMS + 1];   // points before the item
   const int lane = (int)threadIdx.x;
   const uint64_t lt = (1ull << lane) - 1ull;
-  const uint32_t all = (1u << cams.n) - 1u;
+  uint32_t all = 0u;  // the group's cameras
+  for (int c = (int)blockIdx.y; c < cams.n; c += (int)gridDim.y) all |= 1u << c;
   int n_items = 0;                    // wave-uniform
   unsigned long long n_points = 0ull; // wave-uniform
   unsigned n_in = 0, n_vis = 0, n_ovf = 0;
@@ -248,8 +265,8 @@ __global__ void __launch_bounds__(64) k_mask_grad(const float* V, const int32_t*
     wave_lds_sync();
   };
 
-  const int64_t s0 = (int64_t)blockIdx.x * MASK_SLOTS, s1 = 3 * (int64_t)nf;
-  for (int64_t b0 = s0; b0 < s0 + MASK_SLOTS && b0 < s1; b0 += 64) {
+  const int64_t s0 = (int64_t)blockIdx.x * per, s1 = 3 * (int64_t)nf;
+  for (int64_t b0 = s0; b0 < s0 + per && b0 < s1; b0 += 64) {
     const int64_t s = b0 + lane;
     uint32_t todo = 0u, fa = 0u;  // cameras whose outline holds this slot's edge
     int f = 0, twin = -1;
@@ -390,8 +407,9 @@ extern "C" dt_status dt_mask_backward(const dt_scene* sc, const dt_rays* rays, c
                      dim3(256), 0, s, dV, 3 * (int64_t)sc->nv, (unsigned long long*)counts);
   hipLaunchKernelGGL(k_mask_facing, dim3(dt_blocks(sc->nf, MT)), dim3(MT), 0, s, sc->V, sc->F, sc->nv, sc->nf, mc,
                      facing);
-  hipLaunchKernelGGL(k_mask_grad, dim3(dt_blocks(slots, MASK_SLOTS)), dim3(64), 0, s, sc->V, sc->F, sc->nv, sc->nf,
-                     bv, facing, mc, grad_mask, rho, dV, (unsigned long long*)counts);
+  const MaskCut cut = mask_cut(slots, mc.n);
+  hipLaunchKernelGGL(k_mask_grad, dim3(dt_blocks(slots, cut.per), cut.groups), dim3(64), 0, s, sc->V, sc->F, sc->nv,
+                     sc->nf, bv, facing, mc, grad_mask, rho, dV, (unsigned long long*)counts, cut.per);
   DT_CHECK_LAUNCH();
   return DT_OK;
 }
