@@ -53,13 +53,13 @@ MEASURED_TRAFFIC = {
         "sources": ["paper_2603_00413_amd/csrc/trace.hip", "paper_2603_00413_amd/csrc/dt_device.h",
                     "paper_2603_00413_amd/csrc/dt_internal.h", "paper_2603_00413_amd/csrc/dt_queue.h",
                     "paper_2603_00413_amd/csrc/bvh.hip"],
-        "sha256": "383f3845485d560767ed2615a8f21f4fc169158bcfd343f7a8696a05d941f303",
-        "bytes": (271110.7 * 2.0 + 77341.0) * 1024,
+        "sha256": "0cbdd5de81b924321d1c7441a27693f6e8cf5e6607b2a99afed187c4343ee383",
+        "bytes": (271174.9 * 2.0 + 77341.1) * 1024,
         # rocprofv3 --pmc SQ_INSTS_VALU SQ_THREAD_CYCLES_VALU SQ_ACTIVE_INST_VALU:
         # wave-level VALU instructions per launch, and the share of lanes active
         # in them
-        "valu_insts": 2.018e8,
-        "lane_utilization": 0.642,
+        "valu_insts": 2.059e8,
+        "lane_utilization": 0.641,
     },
 }
 

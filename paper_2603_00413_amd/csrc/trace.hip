@@ -1261,10 +1261,11 @@ __global__ void k_grid_gather(const float* copies, int n_copies, int nx, int ny,
 // lanes with one atomic per value into that cell's record (grid records of
 // FG_GREC floats, plane records of FG_PREC), in copy blockIdx.x % copies;
 // k_field_gather turns the records into node values.  Neighbouring rays
-// sample the same cells, so a wave's atomics shrink to a few per cell.  What is
-// left is bound by them: float atomics are carried out at the memory side, and
-// the kernel's time over the generations is 0.13 ms + 48 us per million
-// requests (6 to 19 million; its arithmetic would take 0.1 ms).
+// sample the same cells, so a wave's atomics shrink to a few per cell.  Large
+// generations are bound by those that are left: float atomics are carried out at
+// the memory side, 1,015 us for 18 million requests, 790 for 13.6, 564 for 9.0 (50
+// us a million).  Below 5 million the walk of the sorted records takes some 450 us
+// (its arithmetic at full issue would take 0.1 ms).
 constexpr int FG_T = 256;
 constexpr int FG_GREC = 32;  // 8 corners x 4 channels
 constexpr int FG_PREC = 16;  // 4 corners x 4 channels
